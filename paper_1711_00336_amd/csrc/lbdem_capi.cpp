@@ -513,67 +513,57 @@ void upload_vec(lbdem_domain_t h, double *dev, const double *host, int64_t n)
     hip_check(hipStreamSynchronize(h->stream), "sync");
 }
 
-void download_vec(lbdem_domain_t h, const double *dev, double *host, int64_t n)
-{
-    if (n == 0 || !host) return;
-    std::vector<double> buf(3 * (size_t)n);
-    for (int a = 0; a < 3; ++a)
-        hip_check(hipMemcpyAsync(buf.data() + a * n, dev + a * h->pt.cap, sizeof(double) * n, hipMemcpyDeviceToHost,
-                                 h->stream), "download");
-    hip_check(hipStreamSynchronize(h->stream), "sync");
-    for (int64_t i = 0; i < n; ++i)
-        for (int a = 0; a < 3; ++a) host[3 * i + a] = buf[a * n + i];
-}
-
 struct HostParticles {
     std::vector<double> x, u, w, a, d, rho;
 };
 
-std::vector<int> fetch_ids(lbdem_domain_t h)
+// Particle state in insertion order, [n][3] vectors and [n] scalars, to host
+// or device memory (null pointers are skipped): one kernel reorders the slots
+// into the permutation targets, then each array is one copy. Four vectors of
+// 3.17 M spheres to the host: 31 ms (9.9 GB/s, the copy to pageable memory),
+// 205 ms when the host transposed and scattered every vector itself.
+void read_particle_state(lbdem_domain_t h, hipMemcpyKind kind, double *x, double *u, double *w, double *a, double *d,
+                         double *rho)
 {
-    std::vector<int> id(h->pt.np);
-    if (h->pt.np)
-        hip_check(hipMemcpy(id.data(), h->pt.id, sizeof(int) * h->pt.np, hipMemcpyDeviceToHost), "download");
-    return id;
+    const int64_t n = h->pt.np;
+    const Parts &P = h->pt;
+    double *dst[6] = {x, u, w, a, d, rho};
+    const double *src[6] = {P.x2, P.u2, P.w2, P.a2, P.d2, P.rho2};
+    int what = 0;
+    for (int t = 0; t < 6; ++t) what |= dst[t] ? 1 << t : 0;
+    if (n == 0 || what == 0) return;
+    launch_pack_particles(h->desc(), what, h->stream);
+    hip_check(hipGetLastError(), "particle read-out");
+    for (int t = 0; t < 6; ++t)
+        if (dst[t])
+            hip_check(hipMemcpyAsync(dst[t], src[t], sizeof(double) * (size_t)(t < 4 ? 3 * n : n), kind, h->stream),
+                      "copy");
+    hip_check(hipStreamSynchronize(h->stream), "sync");
 }
 
-// slot-order SoA vector -> insertion-order AoS [n][3]
-void download_vec_ordered(lbdem_domain_t h, const double *dev, double *host, const std::vector<int> &id)
+// forces by insertion index [3][cap] -> host [n][3], through a permutation target
+void download_vec(lbdem_domain_t h, const double *dev, double *host, int64_t n)
 {
-    const int64_t n = (int64_t)id.size();
     if (n == 0 || !host) return;
-    std::vector<double> tmp(3 * n);
-    download_vec(h, dev, tmp.data(), n);
-    for (int64_t s = 0; s < n; ++s)
-        for (int a = 0; a < 3; ++a) host[3 * id[s] + a] = tmp[3 * s + a];
-}
-
-void download_scalar_ordered(lbdem_domain_t h, const double *dev, double *host, const std::vector<int> &id)
-{
-    const int64_t n = (int64_t)id.size();
-    if (n == 0 || !host) return;
-    std::vector<double> tmp(n);
-    hip_check(hipMemcpy(tmp.data(), dev, sizeof(double) * n, hipMemcpyDeviceToHost), "download");
-    for (int64_t s = 0; s < n; ++s) host[id[s]] = tmp[s];
+    launch_pack_vec(dev, h->pt.cap, n, h->pt.x2, h->stream);
+    hip_check(hipGetLastError(), "particle read-out");
+    hip_check(hipMemcpyAsync(host, h->pt.x2, sizeof(double) * 3 * (size_t)n, hipMemcpyDeviceToHost, h->stream),
+              "copy");
+    hip_check(hipStreamSynchronize(h->stream), "sync");
 }
 
 HostParticles fetch_particles(lbdem_domain_t h)
 {
     HostParticles hp;
     const int64_t n = h->pt.np;
-    const std::vector<int> id = fetch_ids(h);
     hp.x.resize(3 * n);
     hp.u.resize(3 * n);
     hp.w.resize(3 * n);
     hp.a.resize(3 * n);
     hp.d.resize(n);
     hp.rho.resize(n);
-    download_vec_ordered(h, h->pt.x, hp.x.data(), id);
-    download_vec_ordered(h, h->pt.u, hp.u.data(), id);
-    download_vec_ordered(h, h->pt.w, hp.w.data(), id);
-    download_vec_ordered(h, h->pt.a, hp.a.data(), id);
-    download_scalar_ordered(h, h->pt.d, hp.d.data(), id);
-    download_scalar_ordered(h, h->pt.rho, hp.rho.data(), id);
+    read_particle_state(h, hipMemcpyDeviceToHost, hp.x.data(), hp.u.data(), hp.w.data(), hp.a.data(), hp.d.data(),
+                        hp.rho.data());
     return hp;
 }
 
@@ -1053,21 +1043,9 @@ lbdem_status lbdem_read_particles(lbdem_domain_t h, int mem_kind, double *x, dou
 {
     if (!h) return fail(nullptr, LBDEM_E_INVALID, "null handle");
     return guarded(h, [&]() -> lbdem_status {
+        read_particle_state(h, mem_kind == LBDEM_MEM_DEVICE ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, x, u,
+                            omega, accel, nullptr, nullptr);
         hip_check(hipStreamSynchronize(h->stream), "sync");
-        const int64_t n = h->pt.np;
-        const std::vector<int> id = fetch_ids(h);
-        const double *src[4] = {h->pt.x, h->pt.u, h->pt.w, h->pt.a};
-        double *dst[4] = {x, u, omega, accel};
-        for (int t = 0; t < 4; ++t) {
-            if (!dst[t]) continue;
-            if (mem_kind == LBDEM_MEM_DEVICE) {
-                std::vector<double> host(3 * n);
-                download_vec_ordered(h, src[t], host.data(), id);
-                hip_check(hipMemcpy(dst[t], host.data(), sizeof(double) * 3 * n, hipMemcpyHostToDevice), "copy");
-            } else {
-                download_vec_ordered(h, src[t], dst[t], id);
-            }
-        }
         return LBDEM_OK;
     });
 }
@@ -1210,13 +1188,7 @@ lbdem_status lbdem_get_state(lbdem_domain_t h, lbdem_state_view *v)
         }
         v->step = h->step_host;
         v->np = h->pt.np;
-        const std::vector<int> id = fetch_ids(h);
-        download_vec_ordered(h, h->pt.x, v->x, id);
-        download_vec_ordered(h, h->pt.u, v->u, id);
-        download_vec_ordered(h, h->pt.w, v->omega, id);
-        download_vec_ordered(h, h->pt.a, v->accel, id);
-        download_scalar_ordered(h, h->pt.d, v->d, id);
-        download_scalar_ordered(h, h->pt.rho, v->rho_p, id);
+        read_particle_state(h, hipMemcpyDeviceToHost, v->x, v->u, v->omega, v->accel, v->d, v->rho_p);
         return LBDEM_OK;
     });
 }

@@ -204,6 +204,10 @@ void launch_bin_build(const Desc &D, hipStream_t s);   // scan + place
 void launch_sort_permute(const Desc &D, hipStream_t s); // order bins, slots <- bin order, stencils
 // the same, with the next subcycle's added-mass force evaluated in the permutation
 template <typename R> void launch_sort_permute_am(const Desc &D, const Cells<R> &C, hipStream_t s);
+// what launch_pack_particles writes (bits)
+enum : int { PACK_X = 1, PACK_U = 2, PACK_W = 4, PACK_A = 8, PACK_D = 16, PACK_RHO = 32 };
+void launch_pack_particles(const Desc &D, int what, hipStream_t s);  // into x2, u2, w2, a2, d2, rho2
+void launch_pack_vec(const double *src, int64_t cap, int64_t n, double *out, hipStream_t s);
 void launch_zero_int(int *p, int64_t n, hipStream_t s);
 void launch_set_step(long long *stepc, long long v, hipStream_t s);
 void launch_set_int(int *p, int v, hipStream_t s);

@@ -2212,6 +2212,35 @@ template <typename A> __global__ void k_vec4_to_soa(const A *src, double *dst, i
         for (int b = 0; b < 3; ++b) dst[b * nc + c] = (double)src[4 * c + b];
 }
 
+// Particle state for the host: slot order [3][cap] -> insertion order [np][3]
+// (one write of 24 contiguous bytes per particle and vector) and [np]
+// scalars, whichever are asked for. Written to the permutation targets, which
+// hold nothing between two reorderings, so reading allocates nothing.
+__global__ __launch_bounds__(kBlock) void k_pack_particles(Desc D, int what)
+{
+    const Parts &P = D.pt;
+    const int64_t s = gidx();
+    if (s >= P.np) return;
+    const int64_t id = P.id[s];
+    const double *vec[4] = {P.x, P.u, P.w, P.a};
+    double *out[4] = {P.x2, P.u2, P.w2, P.a2};
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+        if (what & (1 << t))
+#pragma unroll
+            for (int a = 0; a < 3; ++a) out[t][3 * id + a] = vec[t][a * P.cap + s];
+    if (what & PACK_D) P.d2[id] = P.d[s];
+    if (what & PACK_RHO) P.rho2[id] = P.rho[s];
+}
+// force by insertion index [3][cap] -> [np][3]
+__global__ __launch_bounds__(kBlock) void k_pack_vec(const double *src, int64_t cap, int64_t n, double *out)
+{
+    const int64_t i = gidx();
+    if (i >= n) return;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) out[3 * i + a] = src[a * cap + i];
+}
+
 __global__ void k_set_step(long long *s, long long v) { *s = v; }
 __global__ void k_set_int(int *p, int v) { *p = v; }
 
@@ -2480,6 +2509,14 @@ template <typename R> void launch_sort_permute_am(const Desc &D, const Cells<R> 
 {
     hipLaunchKernelGGL(k_cellsort, dim3(nblocks(D.g.nc)), dim3(kBlock), 0, s, D);
     if (D.pt.np > 0) hipLaunchKernelGGL(k_permute_am<R>, dim3(nblocks(D.pt.np)), dim3(kBlock), 0, s, D, C);
+}
+void launch_pack_particles(const Desc &D, int what, hipStream_t s)
+{
+    if (D.pt.np > 0) hipLaunchKernelGGL(k_pack_particles, dim3(nblocks(D.pt.np)), dim3(kBlock), 0, s, D, what);
+}
+void launch_pack_vec(const double *src, int64_t cap, int64_t n, double *out, hipStream_t s)
+{
+    if (n > 0) hipLaunchKernelGGL(k_pack_vec, dim3(nblocks(n)), dim3(kBlock), 0, s, src, cap, n, out);
 }
 void launch_zero_int(int *p, int64_t n, hipStream_t s) { launch_zero<int>(p, n, s); }
 void launch_set_int(int *p, int v, hipStream_t s)

@@ -1,5 +1,7 @@
 """Launch paths that a domain's size, density or precision selects, each
 against the general path or the FP64 oracle."""
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -39,3 +41,33 @@ def test_crowded_gather_tiles_bitwise_equal(L, eps, d, precision):
             ref = st
         for k in ref:
             assert np.array_equal(np.asarray(ref[k]), np.asarray(st[k])), (v, k)
+
+
+@pytest.mark.parametrize("n", [1, 255, 257, 1000])
+def test_particle_read_out_orders(L, n):
+    """Read-outs return insertion order, whatever the slot order, to host and
+    to device memory."""
+    import torch
+    p = I.Params(n=(21, 17, 30), periodic=(1, 1, 0), tau=0.8, precision="fp64")
+    parts = I.make_particles(2, p, n, 0.5, 0.5, 2.5)
+    rng = np.random.default_rng(n)
+    parts.u[:] = rng.normal(size=(n, 3)) * 1e-4
+    parts.w[:] = rng.normal(size=(n, 3)) * 1e-4
+    parts.d[:] = 0.5 - 0.1 * rng.random(n)
+    parts.rho_p[:] = 2.0 + rng.random(n)
+    with L.Domain(p) as dom:
+        dom.add(parts)
+        st = dom.lbdem_get_state()
+        for k, v in dict(x=parts.x, u=parts.u, w=parts.w, d=parts.d, rho_p=parts.rho_p).items():
+            assert np.array_equal(st[k], v), k
+        dom.step(2)
+        host = dom.lbdem_read_particles()
+        dev = [torch.zeros(n, 3, dtype=torch.float64, device="cuda") for _ in range(4)]
+        torch.cuda.synchronize()
+        ptr = [C.c_void_p(t.data_ptr()) for t in dev]
+        assert L.lib().lbdem_read_particles(dom.h, L.MEM_DEVICE, *ptr) == L.OK
+        for a, b in zip(host, dev):
+            assert np.array_equal(a, b.cpu().numpy())
+        only_w = np.zeros((n, 3))
+        assert L.lib().lbdem_read_particles(dom.h, L.MEM_HOST, None, None, C.c_void_p(only_w.ctypes.data), None) == L.OK
+        assert np.array_equal(only_w, host[2])
