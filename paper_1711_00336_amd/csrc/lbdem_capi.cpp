@@ -60,7 +60,7 @@ struct lbdem_domain {
     Geo geo{};
     Phys phys{};
     Tune tune{-1, -1, -1, -1};
-    int64_t version = 0;        // bumped whenever the particle set is replaced
+    int64_t version = 0;        // bumped whenever captured steps become stale
     std::string err;
     int64_t step_host = 0;
 
@@ -87,13 +87,15 @@ struct lbdem_domain {
     int64_t tmp_len = 0;
     std::vector<void *> owned;
 
-    // captured steps, keyed by (PDF buffer, particle buffer parity)
+    // captured steps, keyed by (PDF buffer, DEM record buffer)
     bool use_graphs = true;
-    int pswap = 0;
+    int rswap = 0;
     hipGraphExec_t graph[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};
 
+    // the captured steps no longer hold; a batch finds that out from version
     void drop_graphs()
     {
+        version += 1;
         for (auto &row : graph)
             for (auto &g : row)
                 if (g) {
@@ -354,11 +356,9 @@ void ensure_lists(lbdem_domain_t h)
     need = std::min(std::max((need + 3) & ~3, 32), 4096);
     if (P.nlist && need <= P.nbr && h->nlist_rows >= P.cap) return;
     h->dfree(P.nlist);
-    h->dfree(P.nslot);
-    P.nlist = P.nslot = nullptr;
+    P.nlist = nullptr;
     P.nbr = std::max(need, P.nbr);
     P.nlist = (int *)h->dalloc(sizeof(int) * (size_t)P.nbr * (size_t)P.cap);
-    P.nslot = (int *)h->dalloc(sizeof(int) * (size_t)P.nbr * (size_t)P.cap);
     h->nlist_rows = P.cap;
 }
 
@@ -374,47 +374,29 @@ void update_body_force(lbdem_domain_t h, const std::vector<double> &d, const std
     for (int a = 0; a < 3; ++a) h->phys.fb[a] = all_per ? -s * p.gravity[a] : 0.0;
 }
 
-void swap_particle_buffers(lbdem_domain_t h)
+// Fused substeps alternate between the two record buffers: after an odd number
+// of them the records are in the other one. Returns whether a step changes it.
+bool step_swaps_records(lbdem_domain_t h)
 {
-    Parts &P = h->pt;
-    h->pswap ^= 1;
-    std::swap(P.x, P.x2);
-    std::swap(P.u, P.u2);
-    std::swap(P.w, P.w2);
-    std::swap(P.a, P.a2);
-    std::swap(P.d, P.d2);
-    std::swap(P.rho, P.rho2);
-    std::swap(P.id, P.id2);
-    std::swap(P.bslot, P.bslot2);
-    std::swap(P.pk, P.pk2);
+    return dem_substep_fused(h->desc()) && (h->phys.n_int & h->phys.n_dem & 1);
 }
 
-// bins of the current positions, slots sorted into bin order, stencils
-void sort_particles(lbdem_domain_t h)
+void swap_records(lbdem_domain_t h)
 {
-    launch_bin_build(h->desc(), h->stream);
-    launch_sort_permute(h->desc(), h->stream);
-    swap_particle_buffers(h);
-    launch_dem_order(h->desc(), h->stream);
-}
-
-// the same, and the next subcycle's added-mass force of every particle
-template <typename R>
-void sort_particles_am(lbdem_domain_t h)
-{
-    launch_bin_build(h->desc(), h->stream);
-    launch_sort_permute_am<R>(h->desc(), h->cells<R>(), h->stream);
-    swap_particle_buffers(h);
-    launch_dem_order(h->desc(), h->stream);
+    h->rswap ^= 1;
+    std::swap(h->pt.pk, h->pt.pk2);
 }
 
 template <typename R>
 void rebuild_particle_fields(lbdem_domain_t h)
 {
     launch_set_int(h->pt.need, 1, h->stream);
+    launch_set_int(h->pt.need + 1, 1, h->stream);
     launch_zero_int(h->cnt, h->geo.nc, h->stream);
     launch_bin_count(h->desc(), h->stream);
-    sort_particles(h);
+    launch_bin_build(h->desc(), h->stream);
+    launch_reorder(h->desc(), h->stream);
+    launch_set_int(h->pt.need + 1, 0, h->stream);
     launch_gather_eps<R>(h->desc(), h->cells<R>(), h->stream);
     hip_check(hipGetLastError(), "particle field rebuild");
 }
@@ -439,7 +421,7 @@ void alloc_particles(lbdem_domain_t h, int64_t cap)
         vec.push_back(&P.Fl_id);
     }
     double **sca[] = {&P.d, &P.rho, &P.d2, &P.rho2};
-    int **ints[] = {&P.id, &P.id2, &P.bslot, &P.bslot2};
+    int **ints[] = {&P.id, &P.id2};
     for (double **v : vec) { h->dfree(*v); *v = nullptr; }
     for (double **v : sca) { h->dfree(*v); *v = nullptr; }
     for (int **v : ints) { h->dfree(*v); *v = nullptr; }
@@ -465,13 +447,13 @@ void alloc_particles(lbdem_domain_t h, int64_t cap)
         *v = (int *)h->dalloc(sizeof(int) * c);
         hip_check(hipMemsetAsync(*v, 0, sizeof(int) * c, h->stream), "hipMemsetAsync");
     }
-    for (int **v : {&P.nlist, &P.nnb, &P.slot_of, &P.nslot}) h->dfree(*v);
+    h->dfree(P.nlist);
+    h->dfree(P.nnb);
     h->dfree(P.xbuild);
-    P.nlist = P.nslot = nullptr;
+    P.nlist = nullptr;
     P.nbr = 0;
     h->nlist_rows = 0;
     P.nnb = (int *)h->dalloc(sizeof(int) * c);
-    P.slot_of = (int *)h->dalloc(sizeof(int) * c);
     P.xbuild = (double *)h->dalloc(sizeof(double) * 3 * c);
     hip_check(hipMemsetAsync(P.nnb, 0, sizeof(int) * c, h->stream), "hipMemsetAsync");
     hip_check(hipMemsetAsync(P.xbuild, 0, sizeof(double) * 3 * c, h->stream), "hipMemsetAsync");
@@ -570,7 +552,6 @@ HostParticles fetch_particles(lbdem_domain_t h)
 void put_particles(lbdem_domain_t h, const HostParticles &hp)
 {
     h->drop_graphs();
-    h->version += 1;
     const int64_t n = (int64_t)hp.d.size();
     if (n > h->pt.cap) alloc_particles(h, std::max<int64_t>(n, 2 * h->pt.cap));
     h->pt.np = n;
@@ -661,6 +642,7 @@ void enqueue_step(lbdem_domain_t h)
     const Cells<R> C = h->cells<R>();
     const int nint = h->phys.n_int;
     const bool lift = h->phys.use_lift != 0;
+    launch_cls(h, 11, [&] { launch_reorder(h->desc(), s); });
     launch_cls(h, 1, [&] { launch_moments<R>(h->desc(), C, s); });
     launch_cls(h, 2, [&] { launch_cellfields<R>(h->desc(), C, s); });
     if (lift) launch_cls(h, 12, [&] { launch_curl<R>(h->desc(), C, s); });
@@ -668,23 +650,22 @@ void enqueue_step(lbdem_domain_t h)
     launch_cls(h, 5, [&] { launch_gather_am<R>(h->desc(), C, s); });
     for (int k = 0; k < nint; ++k) {
         const int last_sub = k == nint - 1;
+        // the lists before the drag spreading, which clears the rebuild request
+        launch_cls(h, 8, [&] { launch_nlist(h->desc(), k == 0, s); });
         launch_cls(h, 4, [&] { launch_part_drag<R>(h->desc(), C, last_sub, s); });
         launch_cls(h, 6, [&] { launch_gather_fd<R>(h->desc(), C, s); });
-        launch_cls(h, 8, [&] { launch_nlist(h->desc(), s); });
-        const bool fused = dem_substep_fused(h->desc());
         for (int sub = 0; sub < h->phys.n_dem; ++sub) {
             const int last_dem = sub == h->phys.n_dem - 1;
-            if (fused) {
-                launch_cls(h, 9, [&] { launch_dem_substep_fused(h->desc(), sub, last_dem, s); });
+            if (dem_substep_fused(h->desc())) {
+                if constexpr (sizeof(R) == 4)
+                    launch_cls(h, 9, [&] { launch_dem_substep_fused(h->desc(), C, sub, last_dem, last_sub, s); });
             } else {
-                launch_cls(h, 9, [&] { launch_dem_force(h->desc(), s); });
-                launch_cls(h, 10, [&] { launch_integrate(h->desc(), last_dem, s); });
+                launch_cls(h, 9, [&] { launch_dem_force<R>(h->desc(), C, s); });
+                launch_cls(h, 10, [&] { launch_integrate<R>(h->desc(), C, last_dem, last_sub, s); });
             }
         }
-        // without lift the next subcycle's added mass is evaluated in the
-        // reordering pass, which holds every particle's new stencil
-        if (!last_sub && !lift) launch_cls(h, 11, [&] { sort_particles_am<R>(h); });
-        else launch_cls(h, 11, [&] { sort_particles(h); });
+        if (dem_substep_fused(h->desc()) && (h->phys.n_dem & 1)) swap_records(h);
+        launch_cls(h, 11, [&] { launch_bin_build(h->desc(), s); });
         if (!last_sub && lift) {
             launch_cls(h, 7, [&] { launch_gather_eps_uf<R>(h->desc(), C, s); });
             launch_cls(h, 12, [&] { launch_curl<R>(h->desc(), C, s); });
@@ -712,7 +693,7 @@ void run_step(lbdem_domain_t h)
         enqueue_step<R>(h);
         return;
     }
-    hipGraphExec_t &ge = h->graph[h->cur][h->pswap];
+    hipGraphExec_t &ge = h->graph[h->cur][h->rswap];
     if (!ge) {
         hipGraph_t g = nullptr;
         hip_check(hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal), "hipStreamBeginCapture");
@@ -728,7 +709,7 @@ void run_step(lbdem_domain_t h)
         // undo the bookkeeping of the capture; the launch below redoes it
         h->cur ^= 1;
         h->step_host -= 1;
-        if (h->phys.n_int & 1) swap_particle_buffers(h);
+        if (step_swaps_records(h)) swap_records(h);
         hipError_t e = hipGraphInstantiate(&ge, g, nullptr, nullptr, 0);
         (void)hipGraphDestroy(g);
         hip_check(e, "hipGraphInstantiate");
@@ -736,7 +717,7 @@ void run_step(lbdem_domain_t h)
     hip_check(hipGraphLaunch(ge, h->stream), "hipGraphLaunch");
     h->cur ^= 1;
     h->step_host += 1;
-    if (h->phys.n_int & 1) swap_particle_buffers(h);
+    if (step_swaps_records(h)) swap_records(h);
 }
 
 template <typename R>
@@ -1306,6 +1287,17 @@ lbdem_status lbdem_load_state(lbdem_domain_t h, const void *blob, size_t size)
 // with the volume-fraction gather (idempotent: it rewrites the same field)
 // and keep the fastest. Variants give bit-identical results.
 // --------------------------------------------------------------------------
+// slots into the current choice of order, lists rebuilt for it
+template <typename R>
+static void reorder_now(lbdem_domain_t h)
+{
+    launch_set_int(h->pt.need + 1, 1, h->stream);
+    launch_reorder(h->desc(), h->stream);
+    launch_nlist(h->desc(), 1, h->stream);
+    launch_set_int(h->pt.need, 0, h->stream);
+    hip_check(hipGetLastError(), "reordering");
+}
+
 template <typename R>
 static void autotune_impl(lbdem_domain_t h)
 {
@@ -1340,7 +1332,6 @@ static void autotune_impl(lbdem_domain_t h)
     // shapes (each particle's force is the same in every order). The lists
     // are brought up to date first, as the pass assumes.
     if (h->pt.np > 0) {
-        launch_nlist(h->desc(), h->stream);
         struct Cand {
             int order, bx, by, bz;
         };
@@ -1350,11 +1341,11 @@ static void autotune_impl(lbdem_domain_t h)
         for (const Cand &c : cand) {
             h->tune.dem_order = c.order;
             if (c.order) set_order_shape(h, c.bx, c.by, c.bz);
-            launch_dem_order(h->desc(), h->stream);
+            reorder_now<R>(h);
             float tmin = 1e30f;
             for (int rep = 0; rep < 4; ++rep) {
                 hip_check(hipEventRecord(a, h->stream), "hipEventRecord");
-                launch_dem_force(h->desc(), h->stream);
+                launch_dem_force<R>(h->desc(), h->cells<R>(), h->stream);
                 hip_check(hipEventRecord(b, h->stream), "hipEventRecord");
                 hip_check(hipEventSynchronize(b), "hipEventSynchronize");
                 float ms = 0.f;
@@ -1370,7 +1361,7 @@ static void autotune_impl(lbdem_domain_t h)
         }
         h->tune.dem_order = best.order;
         set_order_shape(h, best.bx, best.by, best.bz);
-        launch_dem_order(h->desc(), h->stream);
+        reorder_now<R>(h);
         hip_check(hipStreamSynchronize(h->stream), "sync");
     }
 
@@ -1454,7 +1445,7 @@ lbdem_status lbdem_set_tuning(lbdem_domain_t h, const lbdem_tuning *t)
         h->tune.cell_waves = t->cell_waves;
         h->tune.fuse = t->fuse_substep;
         set_order_shape(h, t->dem_block[0], t->dem_block[1], t->dem_block[2]);
-        launch_dem_order(h->desc(), h->stream);
+        launch_set_int(h->pt.need + 1, 1, h->stream);  // the next step starts in the new order
         hip_check(hipStreamSynchronize(h->stream), "sync");
         h->drop_graphs();
         return LBDEM_OK;
@@ -1525,7 +1516,7 @@ std::string batch_key(lbdem_batch_t b)
 {
     std::string k;
     for (lbdem_domain_t d : b->doms)
-        k += std::to_string(d->cur) + ":" + std::to_string(d->pswap) + ":" + std::to_string(d->version) + ";";
+        k += std::to_string(d->cur) + ":" + std::to_string(d->rswap) + ":" + std::to_string(d->version) + ";";
     return k;
 }
 
@@ -1533,7 +1524,7 @@ void advance_bookkeeping(lbdem_domain_t d, int dir)
 {
     d->cur ^= 1;
     d->step_host += dir;
-    if (d->phys.n_int & 1) swap_particle_buffers(d);
+    if (step_swaps_records(d)) swap_records(d);
 }
 
 void batch_drop_graphs(lbdem_batch_t b)

@@ -55,8 +55,8 @@ struct Cells {
 // 1-cell bins: particles sorted by the cell of their position.
 struct Bins {
     int *cnt;                   // [nc] counts (zero between builds)
-    int *start;                 // [nc+1] exclusive prefix of cnt = slot ranges after the permutation
-    int *list;                  // [np] slot indices, ordered by (cell, id) before the permutation
+    int *start;                 // [nc+1] exclusive prefix of cnt: the ranges of list
+    int *list;                  // [np] slots, ordered by (cell, id)
     int *bsum;                  // scan block sums (exclusive prefix after the top-level scan)
     int *loc;                   // [nc] prefix of cnt within its scan block
 };
@@ -75,8 +75,8 @@ struct alignas(64) DemRec {
 static_assert(sizeof(DemRec) == 64, "one 64-byte record");
 
 // Particles, SoA: vectors [3][cap] (component a of slot i at a*cap+i).
-// Slots are kept sorted by (cell, original index) after every rebinning, so
-// a bin is a contiguous slot range and neighbouring threads touch
+// A particle keeps its slot between two list rebuilds, which are preceded by
+// a reordering of the slots by cell, so that neighbouring threads touch
 // neighbouring cells. id[i] is the insertion index of the particle in slot i.
 struct Parts {
     int64_t np, cap;
@@ -93,39 +93,34 @@ struct Parts {
     double *ustart, *xstart;    // velocity / position at subcycle start
     double *Fam_id, *Fd_id, *Fpr_id, *Fc_id;  // last subcycle's forces by insertion index
     double *Fl, *Fl_id;         // lift (slot order; last subcycle by insertion index), lift only
-    // Verlet lists labelled by the slot a particle had when the lists were
-    // built (bslot[slot], carried through the reorders): nlist[label*nbr + t]
-    // holds neighbour labels in ascending insertion index, nnb[label] entries,
-    // build positions xbuild[3][cap] by label; slot_of[label] = current slot;
-    // nslot[label*nbr + t] = slot_of[nlist[label*nbr + t]] (t < nnb[label]),
-    // refreshed with the lists at the start of every subcycle when n_DEM >= 3
-    int *nlist, *nnb, *slot_of, *nslot;
-    int *bslot, *bslot2;        // label of the particle in each slot (+ permutation target)
+    // Verlet lists: nlist[slot*nbr + t] holds neighbour slots in ascending
+    // insertion index, nnb[slot] entries, build positions xbuild[3][cap]
+    int *nlist, *nnb;
     int nbr;                    // list capacity per particle (sized from the density and reach)
     double *xbuild;
-    int *need;                  // 1: rebuild the lists before the next DEM substep
-    DemRec *pk, *pk2;           // packed DEM records by slot (+ permutation target), or null
+    int *need;                  // [0] 1: rebuild the lists before the next DEM substep;
+                                // [1] 1: reorder the slots at the next step's start
+    DemRec *pk, *pk2;           // packed DEM records by slot (+ those of the odd substeps when fused), or null
 };
 
 // launch choices picked per domain (autotuner); -1 = heuristic default
 struct Tune {
     int gather;                 // -1 by density; 0/1/2/4 LDS tiles 16x4x8, 16x4x4, 8x4x4, 16x4x16; 3 per cell
-    int dem_order;              // 0: DEM force pass in slot order; 1: in the blocked order of Order
+    int dem_order;              // slots by cell: 0 row by row, 1 in the blocked order of Order
     int cell_waves;             // workgroups per CU of the streaming cell passes (moments, stream-collide):
                                 // 0 unlimited, else capped through reserved LDS; -1 default
     int fuse;                   // DEM substep forces and integration in one pass where the form
                                 // allows it (FP32 form, n_DEM >= 3): -1 default (off), 0 off, 1 on
 };
 
-// Processing order of the DEM force pass. Slots are sorted by cell in
-// row-major order, so a run of consecutive slots is a thin slab of rows
-// whose neighbours reach two planes up and down. In the blocked order the
-// particles are visited block by block (blocks of ob[0] x ob[1] x ob[2]
+// Blocked slot order. In row-major cell order a run of consecutive slots is a
+// thin slab of rows whose neighbours reach two planes up and down. In the
+// blocked order slots run block by block (blocks of ob[0] x ob[1] x ob[2]
 // cells, each block row by row), so the workgroups in flight on one XCD
 // cover a compact region and their neighbours' records stay in its L2.
 // Each particle's force is the same whatever the order.
 struct Order {
-    int *porder;                // [cap] slot of the v-th particle in blocked order
+    int *porder;                // [cap] place in blocked order of the p-th entry of Bins::list
     int *rowoff;                // [nrows] particles per block row, then their block-local exclusive prefix
     int *rowsum;                // [nrows / kScanPerBlock + 2] scan block sums, then their exclusive prefix
     int64_t nrows;              // block rows: blocks per axis (padded) x ob[1] x ob[2]
@@ -190,20 +185,18 @@ constexpr int64_t kDiagScratchDoubles = (int64_t)kDiagValues * kDiagMaxBlocks + 
 // once per device, with that device current); nullptr if the lookup fails.
 double *diag_scratch_on_device(int device);
 
-void launch_dem_force(const Desc &D, hipStream_t s);
+template <typename R> void launch_dem_force(const Desc &D, const Cells<R> &C, hipStream_t s);
 // FP32 form with n_DEM >= 3 when asked for (tuning): force, torque and the
 // integration of a substep in one pass (records alternate between pk and pk2
 // by substep parity)
 bool dem_substep_fused(const Desc &D);
-void launch_dem_substep_fused(const Desc &D, int sub, int last, hipStream_t s);
-void launch_dem_order(const Desc &D, hipStream_t s);   // blocked processing order of the current slots
-void launch_nlist(const Desc &D, hipStream_t s);      // rebuild Verlet lists if flagged
-void launch_integrate(const Desc &D, int last_substep, hipStream_t s);
+void launch_dem_substep_fused(const Desc &D, const Cells<float> &C, int sub, int last, int step_end, hipStream_t s);
+void launch_reorder(const Desc &D, hipStream_t s);    // slots into list order if due
+void launch_nlist(const Desc &D, int first, hipStream_t s);  // rebuild Verlet lists if flagged
+template <typename R>
+void launch_integrate(const Desc &D, const Cells<R> &C, int last_substep, int step_end, hipStream_t s);
 void launch_bin_count(const Desc &D, hipStream_t s);
-void launch_bin_build(const Desc &D, hipStream_t s);   // scan + place
-void launch_sort_permute(const Desc &D, hipStream_t s); // order bins, slots <- bin order, stencils
-// the same, with the next subcycle's added-mass force evaluated in the permutation
-template <typename R> void launch_sort_permute_am(const Desc &D, const Cells<R> &C, hipStream_t s);
+void launch_bin_build(const Desc &D, hipStream_t s);   // scan, place, order each bin
 // what launch_pack_particles writes (bits)
 enum : int { PACK_X = 1, PACK_U = 2, PACK_W = 4, PACK_A = 8, PACK_D = 16, PACK_RHO = 32 };
 void launch_pack_particles(const Desc &D, int what, hipStream_t s);  // into x2, u2, w2, a2, d2, rho2

@@ -4,10 +4,11 @@
 // Layout: cell fields are structure-of-arrays [ncomp][nc] with x fastest, so
 // a 64-lane wavefront touches 64 consecutive cells of one component. PDFs
 // are stored as deviations f_q - w_q (rho_0 = 1) in float or double.
-// Particles are SoA [3][cap] doubles kept sorted by (cell, insertion index).
-// Particle -> cell transfers are gathers: every cell sums the particles of
-// its 3x3x3 neighbouring 1-cell bins (contiguous slot ranges), so the result
-// is deterministic and needs no floating-point atomics.
+// Particles are SoA [3][cap] doubles in slots that stay put between two list
+// rebuilds; every subcycle sorts only their slot indices by (cell, insertion
+// index). Particle -> cell transfers are gathers: every cell sums the particles
+// of its 3x3x3 neighbouring 1-cell bins (contiguous ranges of the sorted
+// indices), so the result is deterministic and needs no floating-point atomics.
 #include "lbdem_internal.h"
 
 #include <mutex>
@@ -387,6 +388,33 @@ template <typename R> __device__ __forceinline__ void load_stencil(const Parts &
     }
 }
 
+// kernel stencil of a particle at x, stored for slot s; the weights left in st
+// are the stored ones (rounded to FP32 in the FP32 form)
+__device__ __forceinline__ void store_stencil(const Desc &D, int64_t s, const double x[3], Stencil &st)
+{
+    const Parts &P = D.pt;
+    const int64_t cap = P.cap;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        int b;
+        double wt[3];
+        axis_weights(x[a], D.g.n[a], D.g.per[a], b, wt);
+        P.sb[a * cap + s] = b;
+        st.b[a] = b;
+#pragma unroll
+        for (int o = 0; o < 3; ++o) {
+            if (P.swf) {
+                const float f = (float)wt[o];
+                P.swf[(3 * a + o) * cap + s] = f;
+                st.w[a][o] = (double)f;
+            } else {
+                P.sw[(3 * a + o) * cap + s] = wt[o];
+                st.w[a][o] = wt[o];
+            }
+        }
+    }
+}
+
 // st.w[a][o] for a runtime o without indexing a register array
 __device__ __forceinline__ double sel3(const double w[3], int o) { return o == 0 ? w[0] : (o == 1 ? w[1] : w[2]); }
 
@@ -526,8 +554,8 @@ __global__ __launch_bounds__(kBlock) void k_part_am(Desc D, Cells<R> C)
 // ---------------------------------------------------------------------------
 // Gather of a particle quantity to one cell (Eq. distribution_filter with
 // D = I): s = sum_p D(x, x_p) v_p over the particles of the 3x3x3
-// neighbouring bins. Slots are sorted by cell, so each x-row of three bins is
-// one contiguous slot range.
+// neighbouring bins. The slot list is sorted by cell, so each x-row of three
+// bins is one contiguous range of it.
 // ---------------------------------------------------------------------------
 template <typename R>
 __device__ __forceinline__ double stencil_w(const Parts &P, int64_t p, int axis, int ic, int n, int per)
@@ -553,7 +581,8 @@ template <typename R, int NV, typename F>
 __device__ __forceinline__ void gather_range(const Desc &D, int i, int j, int k, int p0, int p1, const F &val,
                                              double *s)
 {
-    for (int p = p0; p < p1; ++p) {
+    for (int q0 = p0; q0 < p1; ++q0) {
+        const int p = D.b.list[q0];
         const R wx = (R)stencil_w<R>(D.pt, p, 0, i, D.g.n[0], D.g.per[0]);
         const R wy = (R)stencil_w<R>(D.pt, p, 1, j, D.g.n[1], D.g.per[1]);
         const R wz = (R)stencil_w<R>(D.pt, p, 2, k, D.g.n[2], D.g.per[2]);
@@ -676,6 +705,7 @@ __device__ __forceinline__ void gather_store(const Desc &D, const Cells<R> &C, i
             const double fext = e * D.p.fb[b] + (double)C.fam[b * nc + c] - s[b];
             C.facc[b * nc + c] = (R)((double)C.facc[b * nc + c] + fext * D.p.dt_int);
         }
+        if (c == 0) D.pt.need[0] = 0;  // the list build of this subcycle is done, its last substep not yet begun
     } else {
         const double e = 1.0 - s[0];
         if (!(e > 0.0) || !isfinite(e)) atomicOr(D.flags, FLAG_EPS);
@@ -704,7 +734,7 @@ __global__ __launch_bounds__(TX *TY *TZ) void k_gather_tile(Desc D, Cells<R> C)
     // FP32 form); products are accumulated in FP64
     __shared__ R sw_l[9][KMAX];
     __shared__ R sv_l[NV][KMAX];
-    __shared__ int sslot[KMAX];  // particle slot of each staged entry
+    __shared__ int sslot[KMAX];  // position in the sorted slot list of each staged entry
 
     const int tid = threadIdx.x;
     const int n0 = D.g.n[0], n1 = D.g.n[1], n2 = D.g.n[2];
@@ -808,7 +838,7 @@ __global__ __launch_bounds__(TX *TY *TZ) void k_gather_tile(Desc D, Cells<R> C)
         while (h1 < HZ && hoff[(h1 + 1) * HX * HY] - base <= KMAX) ++h1;
         const int nk = hoff[h1 * HX * HY] - base;
         if (h0 > 0) __syncthreads();
-        // the particle slot of every staged entry (written by the thread that
+        // the list position of every staged entry (written by the thread that
         // owns the bin: LDS stores only) ...
 #pragma unroll
         for (int t = 0; t < PER; ++t) {
@@ -820,7 +850,7 @@ __global__ __launch_bounds__(TX *TY *TZ) void k_gather_tile(Desc D, Cells<R> C)
         // ... then the staging of weights and values, one entry per thread, so
         // that a wavefront's loads are independent (same entries, same order)
         for (int kk = tid; kk < nk; kk += NT) {
-            const int p = sslot[kk];
+            const int p = D.b.list[sslot[kk]];
 #pragma unroll
             for (int u = 0; u < 9; ++u) sw_l[u][kk] = stencil_weight<R>(P, u, p);
             double v[NV];
@@ -973,8 +1003,9 @@ __global__ __launch_bounds__(kBlock) void k_part_drag(Desc D, Cells<R> C, int re
 
 // ---------------------------------------------------------------------------
 // LDS-tiled particle pass (a6 drag/pressure/gravity, and a4's added mass
-// with lift; without lift the added mass runs per particle). A workgroup owns the particles whose bins lie in a TX x TY x TZ tile of cells
-// (one contiguous slot range per x-row of bins). It loads the cell fields of
+// with lift; without lift the added mass runs per particle). A workgroup owns
+// the particles whose bins lie in a TX x TY x TZ tile of cells (one contiguous
+// range of the sorted slot list per x-row of bins). It loads the cell fields of
 // the tile widened by one cell (wrapped on periodic axes, clamped on walled
 // ones, as the per-particle stencil does) into LDS with coalesced loads, and
 // every particle interpolates from LDS. The arithmetic and its order are
@@ -1066,7 +1097,7 @@ __global__ __launch_bounds__(256) void k_part_tile(Desc D, Cells<R> C, int recor
             if (rp[mid] <= k) lo = mid;
             else hi = mid - 1;
         }
-        const int64_t i = rsrc[lo] + (k - rp[lo]);
+        const int64_t i = D.b.list[rsrc[lo] + (k - rp[lo])];
         Stencil st;
         load_stencil<R>(P, i, st);
         // the stencil base is the particle's bin, inside this tile; the clamp
@@ -1383,6 +1414,10 @@ template <typename T> __device__ __forceinline__ void load_rec(const DemRec *pk,
 // (These kernels have no barriers, so a per-thread check is safe.)
 __device__ __forceinline__ bool halted(const Desc &D) { return *(volatile const int *)D.flags != 0; }
 
+// whether this step starts with a reordering of the slots (need[1] is set
+// during a step and cleared by the first list pass of the next)
+__device__ __forceinline__ bool reorder_due(const Desc &D) { return D.pt.need[1] != 0 && !halted(D); }
+
 __device__ __forceinline__ void min_image(const Geo &g, double dx[3])
 {
 #pragma unroll
@@ -1395,21 +1430,19 @@ __device__ __forceinline__ void min_image(const Geo &g, double dx[3])
 
 // Verlet lists (neighbour search for the sums of Eq. forces_collision,
 // Eq. torques_collision and Eq. lubrication_force, which only reach
-// (d_i + d_j)/2 + h_c). A list holds every particle within that reach plus a
-// skin, as insertion indices sorted ascending, so the force sums run in an
+// (d_i + d_j)/2 + h_c). A list holds the slots of every particle within that
+// reach plus a skin, in ascending insertion index, so the force sums run in an
 // order that does not depend on when the list was built. Rebuilt only when a
-// particle has moved more than (skin/2 - per-subcycle limit) since the build.
-__global__ __launch_bounds__(kBlock) void k_nlist(Desc D)
+// particle has moved more than (skin/2 - per-subcycle limit) since the build;
+// slots do not move between two builds.
+__global__ __launch_bounds__(kBlock) void k_nlist(Desc D, int first)
 {
     const Parts &P = D.pt;
-    if (*P.need == 0 || halted(D)) return;
     const int64_t i = gidx();
+    if (first && i == 0) P.need[1] = 0;
+    if (P.need[0] == 0 || halted(D)) return;
     if (i >= P.np) return;
     const int64_t cap = P.cap;
-    // lists are labelled by the slot at build time (particles keep their
-    // label through the reorders and move little, so labels stay close to
-    // slots and the label-indexed arrays are read almost in order)
-    const int me = (int)i;
     const double xi0 = P.x[i], xi1 = P.x[cap + i], xi2 = P.x[2 * cap + i];
     const double ri = 0.5 * P.d[i];
     const double gap = (D.p.use_lub ? fmax(D.p.h_c, 0.0) : 0.0) + D.p.vskin;
@@ -1424,7 +1457,7 @@ __global__ __launch_bounds__(kBlock) void k_nlist(Desc D)
     const int mz = axis_range(b2, R, D.g.n[2], D.g.per[2], cz, 2 * kMaxR + 1);
     const bool run = mx >= 1 && cx[mx - 1] - cx[0] == mx - 1;
     const int nrun = run ? 1 : mx;
-    int *L = P.nlist + (int64_t)me * P.nbr;
+    int *L = P.nlist + i * P.nbr;
     int m = 0;
     for (int c2 = 0; c2 < mz; ++c2)
         for (int c1 = 0; c1 < my; ++c1)
@@ -1432,16 +1465,17 @@ __global__ __launch_bounds__(kBlock) void k_nlist(Desc D)
                 const int64_t bin = cidx(D.g, cx[c0], cy[c1], cz[c2]);
                 const int p0 = D.b.start[bin];
                 const int p1 = D.b.start[bin + (run ? mx : 1)];
-                for (int j = p0; j < p1; ++j) {
+                for (int q = p0; q < p1; ++q) {
+                    const int j = D.b.list[q];
                     if (j == i) continue;
                     double dx[3] = {P.x[j] - xi0, P.x[cap + j] - xi1, P.x[2 * cap + j] - xi2};
                     min_image(D.g, dx);
                     const double reach = ri + 0.5 * P.d[j] + gap;
                     if (dot3(dx, dx) >= reach * reach) continue;
                     if (m < P.nbr) {
-                        // the neighbour's label (its slot now), kept in
-                        // ascending insertion index, so the pair sums run in
-                        // an order that does not depend on when the list was built
+                        // kept in ascending insertion index, so the pair sums
+                        // run in an order that does not depend on when the list
+                        // was built
                         const int key = P.id[j];
                         int t = m - 1;
                         while (t >= 0 && P.id[L[t]] > key) {
@@ -1457,56 +1491,30 @@ __global__ __launch_bounds__(kBlock) void k_nlist(Desc D)
         atomicOr(D.flags, FLAG_NLIST);
         m = P.nbr;
     }
-    P.nnb[me] = m;
-    P.xbuild[me] = xi0;
-    P.xbuild[cap + me] = xi1;
-    P.xbuild[2 * cap + me] = xi2;
-    P.bslot[i] = me;
-    P.slot_of[me] = (int)i;
+    P.nnb[i] = m;
+    P.xbuild[i] = xi0;
+    P.xbuild[cap + i] = xi1;
+    P.xbuild[2 * cap + i] = xi2;
 }
 
-// The neighbours' current slots, looked up once per subcycle, after the
-// reordering that closed the last subcycle (and any rebuild), for the n_DEM
-// force passes, which then read each neighbour's record without that
-// dependent load (only with n_DEM >= kNslotMinSubsteps substeps, where that
-// saves more than the lookup pass costs). kNslotLanes lanes share a row and
-// take its entries four at a time (rows hold nbr entries, a multiple of
-// four, so each quad is one aligned 16-byte load and store), up to the
-// row's length only: the capacity is about three times the mean length,
-// and a thread per quad of the whole capacity would mostly find nothing to
-// do. The tail of a row's last quad is written as -1.
-constexpr int kNslotMinSubsteps = 3;
-__host__ __device__ __forceinline__ bool use_nslot(const Desc &D) { return D.p.n_dem >= kNslotMinSubsteps; }
-constexpr int kNslotLanes = 8;
-
-__global__ __launch_bounds__(kBlock) void k_nslot(Desc D)
-{
-    const Parts &P = D.pt;
-    if (halted(D)) return;
-    const uint64_t g = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-    const uint64_t row = g / kNslotLanes;
-    if (row >= (uint64_t)P.np) return;
-    const int lane = (int)(g % kNslotLanes);
-    const int n = P.nnb[row];
-    const int64_t rb = (int64_t)row * P.nbr;
-    for (int t = lane * 4; t < n; t += kNslotLanes * 4) {
-        const int4 lab = *reinterpret_cast<const int4 *>(P.nlist + rb + t);
-        int4 out;
-        out.x = P.slot_of[lab.x];
-        out.y = t + 1 < n ? P.slot_of[lab.y] : -1;
-        out.z = t + 2 < n ? P.slot_of[lab.z] : -1;
-        out.w = t + 3 < n ? P.slot_of[lab.w] : -1;
-        *reinterpret_cast<int4 *>(P.nslot + rb + t) = out;
-    }
-}
+// what the last substep of a subcycle does besides integrating
+enum : int {
+    SUB_LAST = 1,  // du_p/dt, kernel stencil of the new position, bin count, list check
+    SUB_AM = 2,    // the next subcycle's added-mass force (without lift, except before a step's end)
+    SUB_END = 4    // the last subcycle of a step: ask for a reordering ahead of the next step
+};
 
 // One semi-implicit Euler substep of particle i (R5: u and omega first,
 // then x) under the contact and lubrication force F and torque Tq of the
 // substep and the subcycle's frozen F_const, with the wall, skin and
-// finiteness checks; rec: where the particle's new DEM record goes (none
-// after the last substep of a subcycle, whose reorder rewrites every record).
-__device__ __forceinline__ void integrate_particle(const Desc &D, int64_t i, int last, const double F[3],
-                                                   const double Tq[3], DemRec *rec)
+// finiteness checks; rec: where the particle's new DEM record goes. The last
+// substep of a subcycle leaves everything that the next one reads of the
+// particle: du_p/dt, the kernel stencil and, while they are in registers, the
+// added-mass force (a4 without lift), so that no separate pass over the
+// particles does it.
+template <typename R>
+__device__ __forceinline__ void integrate_particle(const Desc &D, const Cells<R> &C, int64_t i, int sub,
+                                                   const double F[3], const double Tq[3], DemRec *rec)
 {
     const Parts &P = D.pt;
     const int64_t cap = P.cap;
@@ -1514,16 +1522,17 @@ __device__ __forceinline__ void integrate_particle(const Desc &D, int64_t i, int
     const double m = P.rho[i] * sphere_volume(d);
     const double I = m * d * d / 10.0;
     const double dt = D.p.dt_dem;
-    double x[3];
+    double x[3], u[3], w[3], acc[3];
     int bad = 0;
     double moved = 0.0;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         const int64_t k = a * cap + i;
-        const double u = P.u[k] + dt * (P.Fc[k] + F[a]) / m;
-        P.u[k] = u;
-        P.w[k] = P.w[k] + dt * Tq[a] / I;
-        double xa = P.x[k] + dt * u;
+        u[a] = P.u[k] + dt * (P.Fc[k] + F[a]) / m;
+        P.u[k] = u[a];
+        w[a] = P.w[k] + dt * Tq[a] / I;
+        P.w[k] = w[a];
+        double xa = P.x[k] + dt * u[a];
         const double L = (double)D.g.n[a];
         if (D.g.per[a]) {
             if (xa >= L) xa -= L;
@@ -1534,30 +1543,42 @@ __device__ __forceinline__ void integrate_particle(const Desc &D, int64_t i, int
         } else if (!(xa > 0.0 && xa < L)) {
             bad |= FLAG_WALL;
         }
-        if (!isfinite(xa) || !isfinite(u)) bad |= FLAG_NONFINITE;
+        if (!isfinite(xa) || !isfinite(u[a])) bad |= FLAG_NONFINITE;
         P.x[k] = xa;
         x[a] = xa;
         double dx = xa - P.xstart[k];
         if (D.g.per[a]) dx -= L * rint(dx / L);
         if (fabs(dx) > D.p.skin) bad |= FLAG_SKIN;
-        if (last) P.a[k] = (u - P.ustart[k]) / D.p.dt_int;
-        if (last) {
-            double db = xa - P.xbuild[a * cap + P.bslot[i]];
+        if (sub & SUB_LAST) {
+            acc[a] = (u[a] - P.ustart[k]) / D.p.dt_int;
+            P.a[k] = acc[a];
+            double db = xa - P.xbuild[k];
             if (D.g.per[a]) db -= L * rint(db / L);
             moved = fmax(moved, fabs(db));
         }
     }
     if (bad) atomicOr(D.flags, bad);
     // the record feeds the next substep's pair loop
-    if (rec && !last) {
-        const double uu[3] = {P.u[i], P.u[cap + i], P.u[2 * cap + i]};
-        const double ww[3] = {P.w[i], P.w[cap + i], P.w[2 * cap + i]};
-        store_rec(rec, i, x, uu, ww, d, P.rho[i]);
-    }
+    if (rec) store_rec(rec, i, x, u, w, d, P.rho[i]);
+    if (!(sub & SUB_LAST)) return;
     // with at most `skin` per subcycle, rebuilding once any particle has moved
-    // vskin/2 - skin keeps every pair within the list reach until the rebuild
-    if (last && moved > 0.5 * D.p.vskin - D.p.skin) *P.need = 1;
-    if (last) atomicAdd(&D.b.cnt[particle_cell(D.g, x[0], x[1], x[2])], 1);
+    // vskin/2 - skin keeps every pair within the list reach until the rebuild.
+    // At a step's end the reordering (and with it the rebuild) is asked for a
+    // little earlier, so that rebuilds fall on step starts, after a reordering.
+    const double limit = 0.5 * D.p.vskin - D.p.skin;
+    if (moved > limit) P.need[0] = P.need[1] = 1;
+    else if ((sub & SUB_END) && moved > 0.8 * limit) P.need[1] = 1;
+    atomicAdd(&D.b.cnt[particle_cell(D.g, x[0], x[1], x[2])], 1);
+    // the stencil of a position outside the domain or not finite is not taken
+    // (the step is flagged, the state no longer meaningful)
+    if (bad || halted(D)) return;
+    Stencil st;
+    store_stencil(D, i, x, st);
+    if (sub & SUB_AM) {
+        R Du[3] = {(R)0, (R)0, (R)0};
+        interp_dudt<R>(D, C, st, Du);
+        am_store<R>(D, i, Du, d, acc, u, x);
+    }
 }
 
 // contact + lubrication force and torque on every particle from its list.
@@ -1568,22 +1589,16 @@ __device__ __forceinline__ void integrate_particle(const Desc &D, int64_t i, int
 // whole wavefront would step through the contact code for almost every
 // entry, since some lane nearly always has an overlap there. In the first
 // pass entries are taken three at a time, their indices, slots and particle
-// data requested together so that the memory latencies overlap. With
-// NSLOT the neighbours' current slots come from the subcycle's refreshed
-// copy of the list (k_nslot), saving a dependent load per neighbour;
-// otherwise they are looked up from the labels here. Both sums
+// data requested together so that the memory latencies overlap. Both sums
 // run in list order; lubrication, contacts and the walls are summed apart
 // and added at the end.
-
-template <typename T, bool REC, bool NSLOT, bool FUSE>
-__global__ __launch_bounds__(kBlock) void k_dem_force(Desc D, int last, int odd)
+template <typename T, typename R, bool REC, bool FUSE>
+__global__ __launch_bounds__(kBlock) void k_dem_force(Desc D, Cells<R> C, int sub, int odd)
 {
     static_assert(!FUSE || REC, "the fused substep reads packed records only");
     const Parts &P = D.pt;
-    const int64_t v = gidx();
-    if (v == 0) *P.need = 0;  // lists are current for this subcycle
-    if (v >= P.np) return;
-    const int64_t i = D.t.dem_order ? (int64_t)D.o.porder[v] : v;
+    const int64_t i = gidx();
+    if (i >= P.np) return;
     // FUSE: substeps alternate between the two record buffers, reading the
     // records of the substep's start and writing the integrated ones to the
     // other buffer, so that no thread sees another's update
@@ -1593,10 +1608,8 @@ __global__ __launch_bounds__(kBlock) void k_dem_force(Desc D, int last, int odd)
     else load_pv(P, i, pi);
     T F[3] = {(T)0, (T)0, (T)0}, Tq[3] = {(T)0, (T)0, (T)0}, Fl[3] = {(T)0, (T)0, (T)0};
     const double gap = D.p.use_lub ? fmax(D.p.h_c, 0.0) : 0.0;
-    const int me = P.bslot[i];
-    const int n = P.nnb[me];
-    // the neighbours' slots (NSLOT) or labels, in list order
-    const int *S = (NSLOT ? P.nslot : P.nlist) + (int64_t)me * P.nbr;
+    const int n = P.nnb[i];
+    const int *S = P.nlist + i * P.nbr;
     constexpr int kChunk = 3;
     for (int s0 = 0; s0 < n; s0 += 64) {
         const int s1 = min(n, s0 + 64);
@@ -1605,7 +1618,7 @@ __global__ __launch_bounds__(kBlock) void k_dem_force(Desc D, int last, int odd)
             int js[kChunk];
 #pragma unroll
             for (int c = 0; c < kChunk; ++c)
-                js[c] = t0 + c < s1 ? (NSLOT ? S[t0 + c] : P.slot_of[S[t0 + c]]) : (int)i;
+                js[c] = t0 + c < s1 ? S[t0 + c] : (int)i;
             PV<T> pj[kChunk];
 #pragma unroll
             for (int c = 0; c < kChunk; ++c) {
@@ -1634,7 +1647,7 @@ __global__ __launch_bounds__(kBlock) void k_dem_force(Desc D, int last, int odd)
             const int t = __builtin_ctzll(touch);
             touch &= touch - 1;
             PV<T> pj;
-            const int64_t j = NSLOT ? S[s0 + t] : P.slot_of[S[s0 + t]];
+            const int64_t j = S[s0 + t];
             if constexpr (REC) load_rec(src, j, pj);
             else load_pv(P, j, pj);
             double dx[3] = {pj.x[0] - pi.x[0], pj.x[1] - pi.x[1], pj.x[2] - pi.x[2]};
@@ -1647,7 +1660,7 @@ __global__ __launch_bounds__(kBlock) void k_dem_force(Desc D, int last, int odd)
     const double Fs[3] = {(double)(F[0] + Fl[0]), (double)(F[1] + Fl[1]), (double)(F[2] + Fl[2])};
     const double Ts[3] = {(double)Tq[0], (double)Tq[1], (double)Tq[2]};
     if constexpr (FUSE) {
-        integrate_particle(D, i, last, Fs, Ts, odd ? P.pk : P.pk2);
+        integrate_particle<R>(D, C, i, sub, Fs, Ts, odd ? P.pk : P.pk2);
     } else {
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
@@ -1657,7 +1670,7 @@ __global__ __launch_bounds__(kBlock) void k_dem_force(Desc D, int last, int odd)
     }
 }
 
-// Blocked processing order of the DEM force pass (see Order): block row r
+// Blocked slot order (see Order): block row r
 // = (block, lz, ly) with blocks row-major over the domain and rows y-fastest
 // inside a block; its cells are x0 <= x < x1 of row (y, z). Rows of the
 // padded last blocks that fall outside the domain are empty.
@@ -1687,6 +1700,7 @@ __device__ __forceinline__ int order_row_count(const Desc &D, int x0, int x1, in
 __global__ __launch_bounds__(kBlock) void k_order_scan(Desc D)
 {
     __shared__ int wsum[kBlock / 64];
+    if (!reorder_due(D)) return;
     const int64_t n = D.o.nrows;
     const int64_t base = (int64_t)blockIdx.x * kScanPerBlock + (int64_t)threadIdx.x * kScanItems;
     int v[kScanItems];
@@ -1721,21 +1735,22 @@ __global__ __launch_bounds__(kBlock) void k_order_scan(Desc D)
     if (threadIdx.x == kBlock - 1) D.o.rowsum[blockIdx.x] = btot;
 }
 
-// porder[offset of row r + k] = first slot of row r + k
+// porder[p] = place in the blocked order of the p-th entry of the sorted slot list
 __global__ __launch_bounds__(kBlock) void k_order_fill(Desc D)
 {
+    if (!reorder_due(D)) return;
     const int64_t r = gidx();
-    if (r >= D.o.nrows || halted(D)) return;
+    if (r >= D.o.nrows) return;
     int x0, x1, y, z, s0;
     if (!order_row(D, r, x0, x1, y, z)) return;
     const int cnt = order_row_count(D, x0, x1, y, z, s0);
     const int off = D.o.rowoff[r] + D.o.rowsum[r / kScanPerBlock];
-    for (int k = 0; k < cnt; ++k) D.o.porder[off + k] = s0 + k;
+    for (int k = 0; k < cnt; ++k) D.o.porder[s0 + k] = off + k;
 }
 
 // semi-implicit Euler with the fluid forces frozen (Sec. 3.3); periodic wrap;
-// at the last substep of a subcycle: du_p/dt over the subcycle and bin count
-__global__ __launch_bounds__(kBlock) void k_integrate(Desc D, int last)
+// the last substep of a subcycle also prepares the next one (integrate_particle)
+template <typename R> __global__ __launch_bounds__(kBlock) void k_integrate(Desc D, Cells<R> C, int sub)
 {
     const int64_t i = gidx();
     const Parts &P = D.pt;
@@ -1743,7 +1758,7 @@ __global__ __launch_bounds__(kBlock) void k_integrate(Desc D, int last)
     const int64_t cap = P.cap;
     const double F[3] = {P.Fdem[i], P.Fdem[cap + i], P.Fdem[2 * cap + i]};
     const double Tq[3] = {P.Tdem[i], P.Tdem[cap + i], P.Tdem[2 * cap + i]};
-    integrate_particle(D, i, last, F, Tq, P.pk);
+    integrate_particle<R>(D, C, i, sub, F, Tq, P.pk);
 }
 
 __global__ __launch_bounds__(kBlock) void k_bin_count(Desc D)
@@ -1818,9 +1833,11 @@ __global__ __launch_bounds__(kBlock) void k_scan_block(Desc D)
 }
 
 // exclusive scan of the block sums, one block of 1024 threads
-__global__ __launch_bounds__(1024) void k_scan_top(int *bsum, int nb, int *total)
+// (gate: skipped while *gate is 0)
+__global__ __launch_bounds__(1024) void k_scan_top(int *bsum, int nb, int *total, const int *gate)
 {
     __shared__ int sh[1024];
+    if (gate && *gate == 0) return;
     const int per = (nb + 1023) / 1024;
     const int b0 = threadIdx.x * per;
     int tot = 0;
@@ -1885,81 +1902,63 @@ __global__ __launch_bounds__(kBlock) void k_cellsort(Desc D)
     }
 }
 
-// gather the particle state into bin order (slot s <- list[s]) and evaluate
-// the kernel stencils of the new positions
-// moves the particle bound for slot s into the permutation targets and
-// evaluates its kernel stencil; returns what the fused added-mass pass needs
-__device__ __forceinline__ void permute_slot(const Desc &D, int64_t s, double x[3], double u[3], double acc[3],
-                                             double &d, Stencil &st)
+// Reordering of the slots, at a step's start when the lists are due (need[1]):
+// into the order of the sorted list (cells row by row), or of the blocked order.
+// Particles move far less than a cell between two rebuilds, so the slots stay
+// close to cell order meanwhile, and every pass reads neighbours almost in
+// order; moving the state every subcycle instead cost 338 us of the 14.7 ms
+// subcycle on 3.17 M dense spheres (and a 410 us lookup of the neighbours' new
+// slots), 53 of 340 us on 391 k dilute ones. k_reorder writes the new order to
+// the permutation targets, k_reorder_back copies it home (pointers are baked
+// into captured graphs) and requests the lists.
+__global__ __launch_bounds__(kBlock) void k_reorder(Desc D)
 {
+    if (!reorder_due(D)) return;
     const Parts &P = D.pt;
+    const int64_t p = gidx();
+    if (p >= P.np) return;
     const int64_t cap = P.cap;
-    const int src = D.b.list[s];
-    double w[3];
+    const int src = D.b.list[p];
+    const int64_t s = D.t.dem_order ? (int64_t)D.o.porder[p] : p;
+    double x[3], u[3], w[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         x[a] = P.x[a * cap + src];
         u[a] = P.u[a * cap + src];
         w[a] = P.w[a * cap + src];
-        acc[a] = P.a[a * cap + src];
         P.x2[a * cap + s] = x[a];
         P.u2[a * cap + s] = u[a];
         P.w2[a * cap + s] = w[a];
-        P.a2[a * cap + s] = acc[a];
-        int b;
-        double wt[3];
-        axis_weights(x[a], D.g.n[a], D.g.per[a], b, wt);
-        P.sb[a * cap + s] = b;
-        st.b[a] = b;
-        if (P.swf) {
-#pragma unroll
-            for (int o = 0; o < 3; ++o) {
-                P.swf[(3 * a + o) * cap + s] = (float)wt[o];
-                st.w[a][o] = (double)(float)wt[o];
-            }
-        } else {
-#pragma unroll
-            for (int o = 0; o < 3; ++o) {
-                P.sw[(3 * a + o) * cap + s] = wt[o];
-                st.w[a][o] = wt[o];
-            }
-        }
+        P.a2[a * cap + s] = P.a[a * cap + src];
     }
-    d = P.d[src];
-    const double rho = P.rho[src];
+    const double d = P.d[src], rho = P.rho[src];
     P.d2[s] = d;
     P.rho2[s] = rho;
     P.id2[s] = P.id[src];
-    const int lab = P.bslot[src];
-    P.bslot2[s] = lab;
-    P.slot_of[lab] = (int)s;
-    if (P.pk2) store_rec(P.pk2, s, x, u, w, d, rho);
+    D.b.list[p] = (int)s;
+    Stencil st;
+    store_stencil(D, s, x, st);
+    if (P.pk) store_rec(P.pk, s, x, u, w, d, rho);
 }
 
-__global__ __launch_bounds__(kBlock) void k_permute(Desc D)
+__global__ __launch_bounds__(kBlock) void k_reorder_back(Desc D)
 {
+    if (!reorder_due(D)) return;
+    const Parts &P = D.pt;
     const int64_t s = gidx();
-    if (s >= D.pt.np || halted(D)) return;
-    double x[3], u[3], a[3], d;
-    Stencil st;
-    permute_slot(D, s, x, u, a, d, st);
-}
-
-// the permutation followed by the next subcycle's added-mass force of the
-// particle (a4 without lift): the stencil, position, velocity and du_p/dt are
-// already in registers. The stored-precision weights and the summation order
-// are those of k_part_am, so the forces are bit-identical.
-template <typename R>
-__global__ __launch_bounds__(kBlock) void k_permute_am(Desc D, Cells<R> C)
-{
-    const int64_t s = gidx();
-    if (s >= D.pt.np || halted(D)) return;
-    double x[3], u[3], a[3], d;
-    Stencil st;
-    permute_slot(D, s, x, u, a, d, st);
-    R Du[3] = {(R)0, (R)0, (R)0};
-    interp_dudt<R>(D, C, st, Du);
-    am_store<R>(D, s, Du, d, a, u, x);
+    if (s == 0) P.need[0] = 1;
+    if (s >= P.np) return;
+    const int64_t cap = P.cap;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        P.x[a * cap + s] = P.x2[a * cap + s];
+        P.u[a * cap + s] = P.u2[a * cap + s];
+        P.w[a * cap + s] = P.w2[a * cap + s];
+        P.a[a * cap + s] = P.a2[a * cap + s];
+    }
+    P.d[s] = P.d2[s];
+    P.rho[s] = P.rho2[s];
+    P.id[s] = P.id2[s];
 }
 
 // ---------------------------------------------------------------------------
@@ -2449,45 +2448,47 @@ void launch_diag(const Desc &D, const Cells<R> &C, const R *df, double *partials
     hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(64), 0, s, (const double *)partials, nblk, out);
 }
 
-void launch_dem_force(const Desc &D, hipStream_t s)
+template <typename R> void launch_dem_force(const Desc &D, const Cells<R> &C, hipStream_t s)
 {
     if (D.pt.np == 0) return;
-    const dim3 g(nblocks(D.pt.np)), b(kBlock);
-    const bool ns = use_nslot(D);
-    if (D.pt.pk) {
-        if (ns) hipLaunchKernelGGL((k_dem_force<double, true, true, false>), g, b, 0, s, D, 0, 0);
-        else hipLaunchKernelGGL((k_dem_force<double, true, false, false>), g, b, 0, s, D, 0, 0);
-    } else {
-        if (ns) hipLaunchKernelGGL((k_dem_force<double, false, true, false>), g, b, 0, s, D, 0, 0);
-        else hipLaunchKernelGGL((k_dem_force<double, false, false, false>), g, b, 0, s, D, 0, 0);
+    hipLaunchKernelGGL((k_dem_force<double, R, sizeof(R) == 4, false>), dim3(nblocks(D.pt.np)), dim3(kBlock), 0, s, D, C,
+                       0, 0);
+}
+bool dem_substep_fused(const Desc &D) { return D.pt.pk && D.p.n_dem >= 3 && D.t.fuse == 1; }
+static inline int sub_flags(const Desc &D, int last, int step_end)
+{
+    if (!last) return 0;
+    return SUB_LAST | (step_end ? SUB_END : (D.p.use_lift ? 0 : SUB_AM));
+}
+void launch_dem_substep_fused(const Desc &D, const Cells<float> &C, int sub, int last, int step_end, hipStream_t s)
+{
+    if (D.pt.np == 0) return;
+    hipLaunchKernelGGL((k_dem_force<double, float, true, true>), dim3(nblocks(D.pt.np)), dim3(kBlock), 0, s, D, C,
+                       sub_flags(D, last, step_end), sub & 1);
+}
+// slots into the order of the sorted list, or the blocked one, if due
+void launch_reorder(const Desc &D, hipStream_t s)
+{
+    if (D.pt.np == 0) return;
+    if (D.t.dem_order) {
+        const unsigned nb = nblocks(D.o.nrows, kScanPerBlock);
+        hipLaunchKernelGGL(k_order_scan, dim3(nb), dim3(kBlock), 0, s, D);
+        hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, D.o.rowsum, (int)nb, D.o.rowsum + nb, D.pt.need + 1);
+        hipLaunchKernelGGL(k_order_fill, dim3(nblocks(D.o.nrows)), dim3(kBlock), 0, s, D);
     }
+    hipLaunchKernelGGL(k_reorder, dim3(nblocks(D.pt.np)), dim3(kBlock), 0, s, D);
+    hipLaunchKernelGGL(k_reorder_back, dim3(nblocks(D.pt.np)), dim3(kBlock), 0, s, D);
 }
-bool dem_substep_fused(const Desc &D) { return D.pt.pk && use_nslot(D) && D.t.fuse == 1; }
-void launch_dem_substep_fused(const Desc &D, int sub, int last, hipStream_t s)
-{
-    if (D.pt.np == 0) return;
-    hipLaunchKernelGGL((k_dem_force<double, true, true, true>), dim3(nblocks(D.pt.np)), dim3(kBlock), 0, s, D, last,
-                       sub & 1);
-}
-void launch_dem_order(const Desc &D, hipStream_t s)
-{
-    if (D.pt.np == 0 || !D.t.dem_order) return;
-    const unsigned nb = nblocks(D.o.nrows, kScanPerBlock);
-    hipLaunchKernelGGL(k_order_scan, dim3(nb), dim3(kBlock), 0, s, D);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, D.o.rowsum, (int)nb, D.o.rowsum + nb);
-    hipLaunchKernelGGL(k_order_fill, dim3(nblocks(D.o.nrows)), dim3(kBlock), 0, s, D);
-}
-void launch_nlist(const Desc &D, hipStream_t s)
+void launch_nlist(const Desc &D, int first, hipStream_t s)
 {
     if (D.pt.np <= 0) return;
-    hipLaunchKernelGGL(k_nlist, dim3(nblocks(D.pt.np)), dim3(kBlock), 0, s, D);
-    if (use_nslot(D))
-        hipLaunchKernelGGL(k_nslot, dim3((unsigned)(((uint64_t)D.pt.np * kNslotLanes + kBlock - 1) / kBlock)),
-                           dim3(kBlock), 0, s, D);
+    hipLaunchKernelGGL(k_nlist, dim3(nblocks(D.pt.np)), dim3(kBlock), 0, s, D, first);
 }
-void launch_integrate(const Desc &D, int last, hipStream_t s)
+template <typename R> void launch_integrate(const Desc &D, const Cells<R> &C, int last, int step_end, hipStream_t s)
 {
-    if (D.pt.np > 0) hipLaunchKernelGGL(k_integrate, dim3(nblocks(D.pt.np)), dim3(kBlock), 0, s, D, last);
+    if (D.pt.np > 0)
+        hipLaunchKernelGGL(k_integrate<R>, dim3(nblocks(D.pt.np)), dim3(kBlock), 0, s, D, C,
+                           sub_flags(D, last, step_end));
 }
 void launch_bin_count(const Desc &D, hipStream_t s)
 {
@@ -2497,18 +2498,10 @@ void launch_bin_build(const Desc &D, hipStream_t s)
 {
     const unsigned nb = nblocks(D.g.nc, kScanPerBlock);
     hipLaunchKernelGGL(k_scan_block, dim3(nb), dim3(kBlock), 0, s, D);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, D.b.bsum, (int)nb, D.b.start + D.g.nc);
+    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, D.b.bsum, (int)nb, D.b.start + D.g.nc,
+                       (const int *)nullptr);
     if (D.pt.np > 0) hipLaunchKernelGGL(k_place, dim3(nblocks(D.pt.np)), dim3(kBlock), 0, s, D);
-}
-void launch_sort_permute(const Desc &D, hipStream_t s)
-{
     hipLaunchKernelGGL(k_cellsort, dim3(nblocks(D.g.nc)), dim3(kBlock), 0, s, D);
-    if (D.pt.np > 0) hipLaunchKernelGGL(k_permute, dim3(nblocks(D.pt.np)), dim3(kBlock), 0, s, D);
-}
-template <typename R> void launch_sort_permute_am(const Desc &D, const Cells<R> &C, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_cellsort, dim3(nblocks(D.g.nc)), dim3(kBlock), 0, s, D);
-    if (D.pt.np > 0) hipLaunchKernelGGL(k_permute_am<R>, dim3(nblocks(D.pt.np)), dim3(kBlock), 0, s, D, C);
 }
 void launch_pack_particles(const Desc &D, int what, hipStream_t s)
 {
@@ -2532,7 +2525,8 @@ void launch_set_step(long long *stepc, long long v, hipStream_t s)
     template void launch_moments<R>(const Desc &, const Cells<R> &, hipStream_t);                          \
     template void launch_cellfields<R>(const Desc &, const Cells<R> &, hipStream_t);                       \
     template void launch_curl<R>(const Desc &, const Cells<R> &, hipStream_t);                            \
-    template void launch_sort_permute_am<R>(const Desc &, const Cells<R> &, hipStream_t);                 \
+    template void launch_dem_force<R>(const Desc &, const Cells<R> &, hipStream_t);                       \
+    template void launch_integrate<R>(const Desc &, const Cells<R> &, int, int, hipStream_t);              \
     template void launch_part_am<R>(const Desc &, const Cells<R> &, hipStream_t);                          \
     template void launch_gather_am<R>(const Desc &, const Cells<R> &, hipStream_t);                        \
     template void launch_part_drag<R>(const Desc &, const Cells<R> &, int, hipStream_t);                        \
