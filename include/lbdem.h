@@ -273,7 +273,7 @@ lbdem_status lbdem_load_state(lbdem_domain_t h, const void *blob, size_t size);
  * launches of one kernel class since timing was switched on. Classes:
  * 0 stream-collide, 1 moments, 2 cell fields (Du/Dt, grad P), 3 added-mass
  * particle pass (first subcycle; without lift the later subcycles' added
- * mass runs inside class 11), 4 drag/pressure particle pass, 5 added-mass
+ * mass runs inside class 10, or 9 when fused), 4 drag/pressure particle pass, 5 added-mass
  * spreading, 6 drag spreading and f_acc, 7 volume fraction (+ next
  * added-mass spreading), 8 Verlet list build, 9 DEM contact/lubrication
  * forces, 10 DEM integration, 11 particle binning and reordering, 12

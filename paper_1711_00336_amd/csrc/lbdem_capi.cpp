@@ -318,6 +318,7 @@ void update_search(lbdem_domain_t h)
     Phys &P = h->phys;
     // list build runs on current bins: reach d_max + h_c + Verlet skin
     const double reach = h->dmax + (P.use_lub ? std::max(P.h_c, 0.0) : 0.0) + P.vskin;
+    P.reach_max = reach;
     P.rbin = std::max(1, (int)std::ceil(reach));
     if (P.rbin > 8) throw std::runtime_error("interaction reach d_max + h_c exceeds the 8-cell search limit");
 }
@@ -358,7 +359,10 @@ void ensure_lists(lbdem_domain_t h)
     h->dfree(P.nlist);
     P.nlist = nullptr;
     P.nbr = std::max(need, P.nbr);
-    P.nlist = (int *)h->dalloc(sizeof(int) * (size_t)P.nbr * (size_t)P.cap);
+    // no stale count may meet the new, unwritten lists (a build that flags an
+    // overflow leaves the remaining particles as they were)
+    hip_check(hipMemsetAsync(P.nnb, 0, sizeof(int) * (size_t)P.cap, h->stream), "hipMemsetAsync");
+    P.nlist = (int *)h->dalloc(sizeof(int) * (size_t)P.nbr * (size_t)((P.cap + 63) / 64 * 64));
     h->nlist_rows = P.cap;
 }
 
@@ -396,6 +400,10 @@ void rebuild_particle_fields(lbdem_domain_t h)
     launch_bin_count(h->desc(), h->stream);
     launch_bin_build(h->desc(), h->stream);
     launch_reorder(h->desc(), h->stream);
+    if (dem_sorts_lengths(h->desc())) {  // once more with the lengths known
+        launch_nlist(h->desc(), 0, h->stream);
+        launch_reorder(h->desc(), h->stream);
+    }
     launch_set_int(h->pt.need + 1, 0, h->stream);
     launch_gather_eps<R>(h->desc(), h->cells<R>(), h->stream);
     hip_check(hipGetLastError(), "particle field rebuild");
@@ -411,7 +419,7 @@ void rebuild(lbdem_domain_t h)
 void alloc_particles(lbdem_domain_t h, int64_t cap)
 {
     Parts &P = h->pt;
-    std::vector<double **> vec = {&P.x, &P.u, &P.w, &P.a, &P.x2, &P.u2, &P.w2, &P.a2, &P.Fam, &P.Fd, &P.Fpr, &P.Fc,
+    std::vector<double **> vec = {&P.x, &P.u, &P.w, &P.a, &P.x2, &P.u2, &P.w2, &P.a2, &P.Fam, &P.Fd, &P.Fc,
                                   &P.Fdem, &P.Tdem, &P.ustart, &P.xstart, &P.Fam_id, &P.Fd_id, &P.Fpr_id, &P.Fc_id};
     h->dfree(P.Fl);
     h->dfree(P.Fl_id);
@@ -421,7 +429,7 @@ void alloc_particles(lbdem_domain_t h, int64_t cap)
         vec.push_back(&P.Fl_id);
     }
     double **sca[] = {&P.d, &P.rho, &P.d2, &P.rho2};
-    int **ints[] = {&P.id, &P.id2};
+    int **ints[] = {&P.id, &P.id2, &P.nnb2, &P.pos2};
     for (double **v : vec) { h->dfree(*v); *v = nullptr; }
     for (double **v : sca) { h->dfree(*v); *v = nullptr; }
     for (int **v : ints) { h->dfree(*v); *v = nullptr; }
@@ -471,11 +479,10 @@ void alloc_particles(lbdem_domain_t h, int64_t cap)
     h->dfree(P.pk);
     h->dfree(P.pk2);
     P.pk = P.pk2 = nullptr;
-    if (h->prec == LBDEM_FP32_DEV) {
-        P.pk = (DemRec *)h->dalloc(sizeof(DemRec) * c);
-        P.pk2 = (DemRec *)h->dalloc(sizeof(DemRec) * c);
-        hip_check(hipMemsetAsync(P.pk, 0, sizeof(DemRec) * c, h->stream), "hipMemsetAsync");
-        hip_check(hipMemsetAsync(P.pk2, 0, sizeof(DemRec) * c, h->stream), "hipMemsetAsync");
+    const size_t rec = h->prec == LBDEM_FP32_DEV ? sizeof(DemRec<float>) : sizeof(DemRec<double>);
+    for (void **q : {&P.pk, &P.pk2}) {
+        *q = h->dalloc(rec * c);
+        hip_check(hipMemsetAsync(*q, 0, rec * c, h->stream), "hipMemsetAsync");
     }
     h->dfree(h->ord.porder);
     h->ord.porder = (int *)h->dalloc(sizeof(int) * c);
@@ -657,8 +664,7 @@ void enqueue_step(lbdem_domain_t h)
         for (int sub = 0; sub < h->phys.n_dem; ++sub) {
             const int last_dem = sub == h->phys.n_dem - 1;
             if (dem_substep_fused(h->desc())) {
-                if constexpr (sizeof(R) == 4)
-                    launch_cls(h, 9, [&] { launch_dem_substep_fused(h->desc(), C, sub, last_dem, last_sub, s); });
+                launch_cls(h, 9, [&] { launch_dem_substep_fused<R>(h->desc(), C, sub, last_dem, last_sub, s); });
             } else {
                 launch_cls(h, 9, [&] { launch_dem_force<R>(h->desc(), C, s); });
                 launch_cls(h, 10, [&] { launch_integrate<R>(h->desc(), C, last_dem, last_sub, s); });
@@ -848,6 +854,8 @@ lbdem_status lbdem_create(const lbdem_params *p, void *hip_stream, lbdem_domain_
     h->use_graphs = (p->flags & LBDEM_FLAG_NO_GRAPH) == 0;
     for (int a = 0; a < 3; ++a) {
         h->geo.n[a] = p->n[a];
+        h->geo.len[a] = (double)p->n[a];
+        h->geo.half[a] = 0.5 * (double)p->n[a];
         h->geo.per[a] = p->periodic[a] ? 1 : 0;
     }
     h->geo.nc = nc;

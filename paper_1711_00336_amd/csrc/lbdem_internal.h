@@ -13,6 +13,7 @@ struct Geo {
     int n[3];
     int per[3];
     int64_t nc;
+    double len[3], half[3];     // n and n/2
     // invariant-divisor constants: c / nx and c / (nx*ny) as (umulhi(c,m)+c) >> s
     uint32_t mx, sx, mxy, sxy;
 };
@@ -32,6 +33,7 @@ struct Phys {
     double kn_per_m, xi_per_m;  // k_n / m_ij and xi_n / m_ij from T_c and e_n
     double skin;                // allowed displacement within one subcycle
     double vskin;               // Verlet list skin
+    double reach_max;           // list reach of the largest spheres: d_max + h_c + skin
     int rbin;                   // DEM search radius in cells (list build)
 };
 
@@ -61,18 +63,19 @@ struct Bins {
     int *loc;                   // [nc] prefix of cnt within its scan block
 };
 
-// Packed copy of what a DEM pair evaluation reads of a neighbour, one 64-byte
-// record per slot (FP32-deviation form only): one cache line per neighbour
-// instead of eleven scattered SoA loads. Positions and diameters stay FP64;
-// mass, velocity and spin are rounded to FP32.
-struct alignas(64) DemRec {
+// Packed copy of what a DEM pair evaluation reads of a particle, one record per
+// slot: one or two cache lines per neighbour instead of eleven scattered SoA
+// loads. Positions and diameters are FP64 (the overlap d_i/2 + d_j/2 -
+// |x_j - x_i| cancels); mass, velocity and spin are rounded to the storage
+// precision R. The spin is last: only contacts read it.
+template <typename R> struct alignas(32) DemRec {
     double x[3];
-    double d;                   // FP64: the overlap d_i/2 + d_j/2 - |x_j - x_i| cancels
-    float m;
-    float u[3], w[3];
-    float pad;
+    double d;
+    R m;
+    R u[3], w[3];
+    R pad;
 };
-static_assert(sizeof(DemRec) == 64, "one 64-byte record");
+static_assert(sizeof(DemRec<float>) == 64 && sizeof(DemRec<double>) == 96, "64- and 96-byte records");
 
 // Particles, SoA: vectors [3][cap] (component a of slot i at a*cap+i).
 // A particle keeps its slot between two list rebuilds, which are preceded by
@@ -84,23 +87,24 @@ struct Parts {
     double *d, *rho;            // diameter, density
     int *id;
     double *x2, *u2, *w2, *a2, *d2, *rho2;  // permutation targets
-    int *id2;
+    int *id2, *nnb2, *pos2;
     int *sb;                    // [3][cap] kernel stencil base cell floor(x) per axis
     double *sw;                 // [9][cap] per-axis kernel weights, (3*axis + o+1)*cap + i (FP64 form)
     float *swf;                 // the same in FP32 (FP32-deviation form; exactly one of sw, swf is set)
-    double *Fam, *Fd, *Fpr, *Fc;// current subcycle's fluid forces and F_const (slot order)
+    double *Fam, *Fd, *Fc;      // current subcycle's fluid forces and F_const (slot order)
     double *Fdem, *Tdem;        // contact + lubrication force and torque of the substep
     double *ustart, *xstart;    // velocity / position at subcycle start
     double *Fam_id, *Fd_id, *Fpr_id, *Fc_id;  // last subcycle's forces by insertion index
     double *Fl, *Fl_id;         // lift (slot order; last subcycle by insertion index), lift only
-    // Verlet lists: nlist[slot*nbr + t] holds neighbour slots in ascending
-    // insertion index, nnb[slot] entries, build positions xbuild[3][cap]
+    // Verlet lists: neighbour slots in ascending insertion index, nnb[slot]
+    // entries, those of 64 consecutive slots interleaved (entry t of slot i at
+    // (i/64)*64*nbr + 64 t + i%64); build positions xbuild[3][cap]
     int *nlist, *nnb;
     int nbr;                    // list capacity per particle (sized from the density and reach)
     double *xbuild;
     int *need;                  // [0] 1: rebuild the lists before the next DEM substep;
                                 // [1] 1: reorder the slots at the next step's start
-    DemRec *pk, *pk2;           // packed DEM records by slot (+ those of the odd substeps when fused), or null
+    void *pk, *pk2;             // DemRec<R> by slot (+ those of the odd substeps when fused)
 };
 
 // launch choices picked per domain (autotuner); -1 = heuristic default
@@ -109,8 +113,7 @@ struct Tune {
     int dem_order;              // slots by cell: 0 row by row, 1 in the blocked order of Order
     int cell_waves;             // workgroups per CU of the streaming cell passes (moments, stream-collide):
                                 // 0 unlimited, else capped through reserved LDS; -1 default
-    int fuse;                   // DEM substep forces and integration in one pass where the form
-                                // allows it (FP32 form, n_DEM >= 3): -1 default (off), 0 off, 1 on
+    int fuse;                   // DEM substep forces and integration in one pass: -1 default (on), 0 off, 1 on
 };
 
 // Blocked slot order. In row-major cell order a run of consecutive slots is a
@@ -186,12 +189,13 @@ constexpr int64_t kDiagScratchDoubles = (int64_t)kDiagValues * kDiagMaxBlocks + 
 double *diag_scratch_on_device(int device);
 
 template <typename R> void launch_dem_force(const Desc &D, const Cells<R> &C, hipStream_t s);
-// FP32 form with n_DEM >= 3 when asked for (tuning): force, torque and the
-// integration of a substep in one pass (records alternate between pk and pk2
-// by substep parity)
+// force, torque and the integration of a substep in one pass (records alternate
+// between pk and pk2 by substep parity)
 bool dem_substep_fused(const Desc &D);
-void launch_dem_substep_fused(const Desc &D, const Cells<float> &C, int sub, int last, int step_end, hipStream_t s);
+template <typename R>
+void launch_dem_substep_fused(const Desc &D, const Cells<R> &C, int sub, int last, int step_end, hipStream_t s);
 void launch_reorder(const Desc &D, hipStream_t s);    // slots into list order if due
+bool dem_sorts_lengths(const Desc &D);
 void launch_nlist(const Desc &D, int first, hipStream_t s);  // rebuild Verlet lists if flagged
 template <typename R>
 void launch_integrate(const Desc &D, const Cells<R> &C, int last_substep, int step_end, hipStream_t s);

@@ -71,3 +71,81 @@ def test_particle_read_out_orders(L, n):
         only_w = np.zeros((n, 3))
         assert L.lib().lbdem_read_particles(dom.h, L.MEM_HOST, None, None, C.c_void_p(only_w.ctypes.data), None) == L.OK
         assert np.array_equal(only_w, host[2])
+
+
+def _lattice(n, m, jitter, d_lo, d_hi, rng):
+    """m^3 spheres on a jittered cubic lattice of the box n."""
+    g = np.stack(np.meshgrid(*[np.arange(m)] * 3, indexing="ij"), -1).reshape(-1, 3) + 0.5
+    x = (g + rng.uniform(-jitter, jitter, g.shape) * m / np.min(n)) * (np.asarray(n, float) / m)
+    k = rng.permutation(len(x))
+    return x[k], rng.uniform(d_lo, d_hi, len(x))
+
+
+@pytest.mark.parametrize("name,n,m,d,h_c,n_int,n_dem", [
+    # lists sorted in place (over 512 entries), eight lanes per particle
+    ("long_lists", (10, 10, 10), 20, (0.25, 0.3), 3.0, 2, 1),
+    # eight and two lanes per particle, three substeps
+    ("lanes8", (15, 15, 15), 14, (0.85, 0.95), 1.0, 10, 3),
+    ("lanes2", (40, 38, 39), 36, (0.86, 0.94), 0.9, 4, 3),
+    # one lane per particle, more than 64 list entries
+    ("lanes1", (48, 48, 48), 52, (0.62, 0.9), 1.7, 2, 1),
+])
+def test_dem_lane_counts_match_oracle(L, name, n, m, d, h_c, n_int, n_dem):
+    """The DEM pass with each number of lanes per particle, with contacts,
+    walls and periodic axes, FP64, against the oracle after one step: 1e-12 of
+    the largest value (the bar of the other FP64 parity tests). The separate
+    force and integration passes give the same bits."""
+    from tests.parity_util import compare_states
+    from oracle import oracle as O
+    rng = np.random.default_rng(11)
+    # (far beyond its own diameter the lubrication is not dissipative: kept small)
+    tau = 0.5001 if name == "long_lists" else I.SWEEP_TAU
+    p = I.Params(n=n, periodic=(1, 1, 0), tau=tau, e_n=0.9, h_c=h_c, n_int=n_int, n_dem=n_dem)
+    x, dd = _lattice(n, m, 0.08, d[0], d[1], rng)
+    lo, hi = 0.5 * dd, n[2] - 0.5 * dd
+    x[:, 2] = np.clip(x[:, 2], lo, hi)
+    k = len(x)
+    parts = I.Particles(x, rng.normal(size=(k, 3)) * 1e-4, rng.normal(size=(k, 3)) * 1e-4, dd, np.full(k, 2.5))
+    print(f"{name}: {k} spheres", flush=True)
+    o = O.Oracle(p, parts)
+    assert o.step(1)["status"] == 0
+    ref = None
+    for fuse in (1, 0):
+        with L.Domain(p) as dom:
+            dom.add(parts)
+            dom.lbdem_set_tuning(fuse_substep=fuse)
+            dom.step(1)
+            st = dom.lbdem_get_state()
+        if ref is None:
+            ref = st
+            errs, bad = compare_states(st, o.state, p, 1e-12)
+            print(f"  rel errors {errs}", flush=True)
+            assert not bad, errs
+        for key in ("df", "x", "u", "w", "a"):
+            assert np.array_equal(ref[key], st[key]), key
+
+
+@pytest.mark.parametrize("k", [1, 63, 64, 65, 129])
+@pytest.mark.parametrize("precision,tol", [("fp64", 1e-12), ("fp32dev", 1e-5)])
+def test_few_particles_match_oracle(L, k, precision, tol):
+    """Particle counts around a wavefront, some overlapping, three substeps."""
+    from tests.parity_util import compare_states
+    from oracle import oracle as O
+    rng = np.random.default_rng(k)
+    p = I.Params(n=(12, 13, 14), periodic=(1, 0, 1), tau=0.8, h_c=0.5, n_int=10, n_dem=3, precision=precision)
+    d = np.full(k, 0.8)
+    x = I.place_spheres(k, p.n, p.periodic, d)
+    if k > 1:  # the closest pair overlaps by a hundredth
+        far = np.linalg.norm(x[:, None] - x[None], axis=-1) + 9.0 * np.eye(k)
+        pair = np.unravel_index(far.argmin(), far.shape)
+        d[list(pair)] = 1.01 * far.min()
+    parts = I.Particles(x, rng.normal(size=(k, 3)) * 1e-4, rng.normal(size=(k, 3)) * 1e-4, d, np.full(k, 2.5))
+    o = O.Oracle(p, parts)
+    st0 = o.step(1)
+    assert st0["status"] == 0
+    with L.Domain(p) as dom:
+        dom.add(parts)
+        dom.step(1)
+        errs, bad = compare_states(dom.lbdem_get_state(), o.state, p, tol)
+    print(f"{k} {precision}: {errs}", flush=True)
+    assert not bad, errs
