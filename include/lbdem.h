@@ -283,11 +283,11 @@ lbdem_status lbdem_set_timing(lbdem_domain_t h, int on);
 lbdem_status lbdem_kernel_time(lbdem_domain_t h, int cls, double *ms_total, int64_t *launches);
 
 /* Pick launch shapes for this domain by timing them on its current state:
- * the gather variant (see lbdem_set_gather_variant), the processing order
- * of the DEM force pass (slot order, or block by block with one of a few
- * block shapes, so that the particles in flight on one XCD cover a compact
- * region whose neighbours stay in its L2 cache) and the residency of the
- * streaming cell passes. Results are bit-identical across choices: every
+ * the gather variant (see lbdem_set_gather_variant), the order of the
+ * particle slots (by cell row by row; from 2^18 particles on block by block
+ * with one of two block shapes, so that the particles in flight on one XCD
+ * cover a compact region whose neighbours stay in its L2 cache) and the
+ * residency of the streaming cell passes. Results are bit-identical across choices: every
  * gather variant sums a cell's particles in the same order, each particle's
  * DEM force is the same in any processing order, and the cell passes are
  * cell-local. Optional out: the chosen gather variant. */
@@ -296,21 +296,20 @@ lbdem_status lbdem_autotune(lbdem_domain_t h, int32_t *gather_variant);
 /* Launch choices of a domain (autotuned or set by hand). */
 typedef struct lbdem_tuning {
     int32_t gather_variant;   /* as lbdem_set_gather_variant; -1 automatic by density */
-    int32_t dem_order;        /* DEM force pass: -1 automatic (blocked from 2^20
-                                 particles on), 0 slot order, 1 blocked order */
+    int32_t dem_order;        /* particle slots (and with them the DEM force pass):
+                                 -1 automatic (blocked from 2^18 particles on), 0 by
+                                 cell row by row, 1 by cell in blocks */
     int32_t dem_block[3];     /* block shape of the blocked order in cells, 1..256 each
                                  (default 32 x 32 x 32) */
     int32_t cell_waves;       /* workgroups of 256 threads per CU for the streaming
                                  cell passes (moments, stream-collide), capped with
                                  reserved LDS: -1 default (4 for FP32 storage, none
                                  for FP64), 0 no cap, 1..16 */
-    int32_t fuse_substep;     /* FP32 storage with n_DEM >= 3: the contact and
-                                 lubrication forces of a DEM substep and its
-                                 integration (Sec. 3.1.1) in one pass, the packed
-                                 records alternating between two buffers; -1 default
-                                 (off), 0 off (separate passes), 1 on. Results are
-                                 bit-identical either way; ignored where the form
-                                 does not allow it (FP64 storage, fewer substeps) */
+    int32_t fuse_substep;     /* the contact and lubrication forces of a DEM substep
+                                 and its integration (Sec. 3.1.1) in one pass, the
+                                 packed records alternating between two buffers; -1
+                                 default (on), 0 off (separate passes), 1 on. Results
+                                 are bit-identical either way */
 } lbdem_tuning;
 
 /* Read the domain's launch choices. */
