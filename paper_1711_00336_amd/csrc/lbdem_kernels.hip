@@ -420,7 +420,7 @@ __device__ __forceinline__ double sel3(const double w[3], int o) { return o == 0
 
 // F_am = C_am rho_f V (Du/Dt|p - a_p) (Table 1) of slot i from the particle's
 // diameter, du_p/dt, velocity and position; records the subcycle-start
-// velocity and position
+// velocity and position (a single substep has them at hand)
 template <typename R>
 __device__ __forceinline__ void am_store(const Desc &D, int64_t i, const R Du[3], double d, const double a[3],
                                          const double u[3], const double x[3])
@@ -433,8 +433,10 @@ __device__ __forceinline__ void am_store(const Desc &D, int64_t i, const R Du[3]
     for (int b = 0; b < 3; ++b) {
         const R F = D.p.use_am ? cam * V * (Du[b] - (R)a[b]) : (R)0;
         P.Fam[b * cap + i] = (double)F;
-        P.ustart[b * cap + i] = u[b];
-        P.xstart[b * cap + i] = x[b];
+        if (D.p.n_dem > 1) {
+            P.ustart[b * cap + i] = u[b];
+            P.xstart[b * cap + i] = x[b];
+        }
     }
 }
 
@@ -443,12 +445,14 @@ template <typename R> __device__ __forceinline__ void am_force(const Desc &D, in
 {
     const Parts &P = D.pt;
     const int64_t cap = P.cap;
-    double a[3], u[3], x[3];
+    double a[3], u[3] = {0.0, 0.0, 0.0}, x[3] = {0.0, 0.0, 0.0};
 #pragma unroll
     for (int b = 0; b < 3; ++b) {
         a[b] = P.a[b * cap + i];
-        u[b] = P.u[b * cap + i];
-        x[b] = P.x[b * cap + i];
+        if (D.p.n_dem > 1) {
+            u[b] = P.u[b * cap + i];
+            x[b] = P.x[b * cap + i];
+        }
     }
     am_store<R>(D, i, Du, P.d[i], a, u, x);
 }
@@ -1394,7 +1398,7 @@ template <int N> __device__ __forceinline__ void copy_quads(const void *src, voi
 
 template <typename R>
 __device__ __forceinline__ void store_rec(DemRec<R> *pk, int64_t i, const double x[3], const double u[3],
-                                          const double w[3], double d, double rho)
+                                          const double w[3], double d, R m)
 {
     DemRec<R> r;
 #pragma unroll
@@ -1404,7 +1408,7 @@ __device__ __forceinline__ void store_rec(DemRec<R> *pk, int64_t i, const double
         r.w[a] = (R)w[a];
     }
     r.d = d;
-    r.m = (R)(rho * sphere_volume(d));
+    r.m = m;
     r.pad = (R)0;
     copy_quads<sizeof(DemRec<R>) / 16>(&r, pk + i);
 }
@@ -1628,28 +1632,42 @@ enum : int {
 // particle: du_p/dt, the kernel stencil and, while they are in registers, the
 // added-mass force (a4 without lift), so that no separate pass over the
 // particles does it.
-template <typename R>
+//
+// FUSED: own is the particle's view in the substep's record src. Position,
+// diameter (and the FP64 form's mass) are taken from it and the position goes
+// back to the state arrays at the subcycle's end only; wavefronts without any
+// torque leave the spins alone. A substep then moves 232 B per particle (FP32
+// form, without the lists) instead of 390, a lone substep with everything it
+// leaves for the next subcycle 352 instead of 560.
+template <typename R, bool FUSED>
 __device__ __forceinline__ void integrate_particle(const Desc &D, const Cells<R> &C, int64_t i, int sub,
-                                                   const double F[3], const double Tq[3], DemRec<R> *rec)
+                                                   const double F[3], const double Tq[3], const PV &own,
+                                                   const DemRec<R> *src, DemRec<R> *rec)
 {
     const Parts &P = D.pt;
     const int64_t cap = P.cap;
-    const double d = P.d[i];
-    const double m = P.rho[i] * sphere_volume(d);
+    const bool single = D.p.n_dem == 1;  // the subcycle starts at this substep's start
+    const double d = FUSED ? own.d : P.d[i];
+    const double m = FUSED && sizeof(R) == 8 ? own.m : P.rho[i] * sphere_volume(d);
     const double I = m * d * d / 10.0;
     const double dt = D.p.dt_dem;
     double x[3], u[3], w[3], acc[3];
+    const bool spin = !FUSED || __any(Tq[0] != 0.0 || Tq[1] != 0.0 || Tq[2] != 0.0);
+    if (!spin) load_spin<R>(src, i, w);
     int bad = 0;
     double moved = 0.0;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         const int64_t k = a * cap + i;
-        u[a] = P.u[k] + dt * (P.Fc[k] + F[a]) / m;
+        const double u0 = P.u[k], x0 = FUSED ? own.x[a] : P.x[k];
+        u[a] = u0 + dt * (P.Fc[k] + F[a]) / m;
         P.u[k] = u[a];
-        w[a] = P.w[k] + dt * Tq[a] / I;
-        P.w[k] = w[a];
-        double xa = P.x[k] + dt * u[a];
-        const double L = (double)D.g.n[a];
+        if (spin) {
+            w[a] = P.w[k] + dt * Tq[a] / I;
+            P.w[k] = w[a];
+        }
+        double xa = x0 + dt * u[a];
+        const double L = D.g.len[a];
         if (D.g.per[a]) {
             if (xa >= L) xa -= L;
             else if (xa < 0.0) {
@@ -1660,13 +1678,13 @@ __device__ __forceinline__ void integrate_particle(const Desc &D, const Cells<R>
             bad |= FLAG_WALL;
         }
         if (!isfinite(xa) || !isfinite(u[a])) bad |= FLAG_NONFINITE;
-        P.x[k] = xa;
+        if (!FUSED || (sub & SUB_LAST)) P.x[k] = xa;
         x[a] = xa;
-        double dx = xa - P.xstart[k];
+        double dx = xa - (single ? x0 : P.xstart[k]);
         if (D.g.per[a]) dx -= L * rint(dx / L);
         if (fabs(dx) > D.p.skin) bad |= FLAG_SKIN;
         if (sub & SUB_LAST) {
-            acc[a] = (u[a] - P.ustart[k]) / D.p.dt_int;
+            acc[a] = (u[a] - (single ? u0 : P.ustart[k])) / D.p.dt_int;
             P.a[k] = acc[a];
             double db = xa - P.xbuild[k];
             if (D.g.per[a]) db -= L * rint(db / L);
@@ -1675,7 +1693,7 @@ __device__ __forceinline__ void integrate_particle(const Desc &D, const Cells<R>
     }
     if (bad) atomicOr(D.flags, bad);
     // the record feeds the next substep's pair loop
-    store_rec<R>(rec, i, x, u, w, d, P.rho[i]);
+    store_rec<R>(rec, i, x, u, w, d, FUSED ? (R)own.m : (R)m);
     if (!(sub & SUB_LAST)) return;
     // with at most `skin` per subcycle, rebuilding once any particle has moved
     // vskin/2 - skin keeps every pair within the list reach until the rebuild.
@@ -1769,12 +1787,11 @@ __device__ __forceinline__ void load_pieces(const DemRec<R> *src, uint32_t q16, 
 }
 
 template <typename R, int G, typename Off>
-__device__ __forceinline__ void dem_particle(const Desc &D, const DemRec<R> *src, int64_t i, int l, double Fs[3],
-                                             double Tq[3])
+__device__ __forceinline__ void dem_particle(const Desc &D, const DemRec<R> *src, int64_t i, int l, PV &pi,
+                                             double Fs[3], double Tq[3])
 {
     constexpr int kPieces = rec_pieces<R>();
     const Parts &P = D.pt;
-    PV pi;
     load_rec<R>(src, i, pi);
     double F[3] = {0.0, 0.0, 0.0}, Fl[3] = {0.0, 0.0, 0.0};
 #pragma unroll
@@ -1930,8 +1947,10 @@ __device__ __forceinline__ void dem_particle(const Desc &D, const DemRec<R> *src
 // alternate between the two record buffers (odd: from pk2 to pk), reading the
 // records of the substep's start and writing the integrated ones to the other
 // buffer, so that no thread sees another's update.
+// (4 waves per SIMD in the FP32 form with one lane per particle, which needs 129
+// registers otherwise)
 template <typename R, int G, bool FUSE, typename Off>
-__global__ __launch_bounds__(kBlock) void k_dem_force(Desc D, Cells<R> C, int sub, int odd)
+__global__ __launch_bounds__(kBlock, sizeof(R) == 4 && G == 1 ? 4 : 1) void k_dem_force(Desc D, Cells<R> C, int sub, int odd)
 {
     const Parts &P = D.pt;
     const int64_t v = gidx();
@@ -1944,10 +1963,11 @@ __global__ __launch_bounds__(kBlock) void k_dem_force(Desc D, Cells<R> C, int su
     if (!own) i = P.np - 1;
     DemRec<R> *pk = (DemRec<R> *)P.pk, *pk2 = (DemRec<R> *)P.pk2;
     double F[3], Tq[3];
-    dem_particle<R, G, Off>(D, FUSE && odd ? pk2 : pk, i, l, F, Tq);
+    PV pi;
+    dem_particle<R, G, Off>(D, FUSE && odd ? pk2 : pk, i, l, pi, F, Tq);
     if (!own || (G > 1 && l != 0)) return;
     if constexpr (FUSE) {
-        integrate_particle<R>(D, C, i, sub, F, Tq, odd ? pk : pk2);
+        integrate_particle<R, true>(D, C, i, sub, F, Tq, pi, odd ? pk2 : pk, odd ? pk : pk2);
     } else {
         const int64_t cap = P.cap;
 #pragma unroll
@@ -2046,7 +2066,7 @@ template <typename R> __global__ __launch_bounds__(kBlock) void k_integrate(Desc
     const int64_t cap = P.cap;
     const double F[3] = {P.Fdem[i], P.Fdem[cap + i], P.Fdem[2 * cap + i]};
     const double Tq[3] = {P.Tdem[i], P.Tdem[cap + i], P.Tdem[2 * cap + i]};
-    integrate_particle<R>(D, C, i, sub, F, Tq, (DemRec<R> *)P.pk);
+    integrate_particle<R, false>(D, C, i, sub, F, Tq, PV(), (const DemRec<R> *)nullptr, (DemRec<R> *)P.pk);
 }
 
 __global__ __launch_bounds__(kBlock) void k_bin_count(Desc D)
@@ -2266,8 +2286,9 @@ __global__ __launch_bounds__(kBlock) void k_reorder_back(Desc D)
     D.b.list[P.pos2[s]] = (int)f;
     Stencil st;
     store_stencil(D, f, x, st);
-    if (P.swf) store_rec<float>((DemRec<float> *)P.pk, f, x, u, w, d, rho);
-    else store_rec<double>((DemRec<double> *)P.pk, f, x, u, w, d, rho);
+    const double m = rho * sphere_volume(d);
+    if (P.swf) store_rec<float>((DemRec<float> *)P.pk, f, x, u, w, d, (float)m);
+    else store_rec<double>((DemRec<double> *)P.pk, f, x, u, w, d, m);
 }
 
 // ---------------------------------------------------------------------------
