@@ -666,6 +666,7 @@ void enqueue_step(lbdem_domain_t h)
         launch_cls(h, 6, [&] { launch_gather_fd<R>(h->desc(), C, s); });
         for (int sub = 0; sub < h->phys.n_dem; ++sub) {
             const int last_dem = sub == h->phys.n_dem - 1;
+            if (dem_subcycle_single(h->desc()) && sub > 0) break;  // substep 0 ran them all
             if (dem_substep_fused(h->desc())) {
                 launch_cls(h, 9, [&] { launch_dem_substep_fused<R>(h->desc(), C, sub, last_dem, last_sub, s); });
             } else {

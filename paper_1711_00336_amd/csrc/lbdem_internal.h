@@ -192,6 +192,7 @@ template <typename R> void launch_dem_force(const Desc &D, const Cells<R> &C, hi
 // force, torque and the integration of a substep in one pass (records alternate
 // between pk and pk2 by substep parity)
 bool dem_substep_fused(const Desc &D);
+bool dem_subcycle_single(const Desc &D);
 template <typename R>
 void launch_dem_substep_fused(const Desc &D, const Cells<R> &C, int sub, int last, int step_end, hipStream_t s);
 void launch_reorder(const Desc &D, hipStream_t s);    // slots into list order if due

@@ -1978,6 +1978,33 @@ __global__ __launch_bounds__(kBlock, sizeof(R) == 4 && G == 1 ? 4 : 1) void k_de
     }
 }
 
+// All substeps of a subcycle in one launch of one workgroup, for particles that
+// fit into one (np <= kBlock, one lane each, short lists): a substep of so few
+// takes less time than its launch. The particles meet at a barrier after every substep; the
+// records alternate as above. One sphere at a wall, 50 substeps: 117 us,
+// 280 us as 50 launches (and twice that as 100 with the integration apart).
+template <typename R>
+__global__ __launch_bounds__(kBlock) void k_dem_subcycle(Desc D, Cells<R> C, int sub_last)
+{
+    const Parts &P = D.pt;
+    const bool own = threadIdx.x < P.np;
+    const int64_t i = own ? threadIdx.x : P.np - 1;
+    const bool wave = (int64_t)(threadIdx.x & ~63u) < P.np;  // wavefronts without particles only meet the others
+    DemRec<R> *a = (DemRec<R> *)P.pk, *b = (DemRec<R> *)P.pk2;
+    for (int t = 0; t < D.p.n_dem; ++t) {
+        if (wave) {
+            double F[3], Tq[3];
+            PV pi;
+            dem_particle<R, 1, uint32_t>(D, a, i, 0, pi, F, Tq);
+            if (own) integrate_particle<R, true>(D, C, i, t == D.p.n_dem - 1 ? sub_last : 0, F, Tq, pi, a, b);
+        }
+        __syncthreads();
+        DemRec<R> *c = a;
+        a = b;
+        b = c;
+    }
+}
+
 // Blocked slot order (see Order): block row r
 // = (block, lz, ly) with blocks row-major over the domain and rows y-fastest
 // inside a block; its cells are x0 <= x < x1 of row (y, z). Rows of the
@@ -2820,9 +2847,20 @@ static inline int sub_flags(const Desc &D, int last, int step_end)
     if (!last) return 0;
     return SUB_LAST | (step_end ? SUB_END : (D.p.use_lift ? 0 : SUB_AM));
 }
+// whether a subcycle's substeps run in one launch (enqueued for substep 0 only)
+bool dem_subcycle_single(const Desc &D)
+{
+    return dem_substep_fused(D) && D.p.n_dem > 1 && D.pt.np <= kBlock && dem_lanes(D) == 1;
+}
 template <typename R>
 void launch_dem_substep_fused(const Desc &D, const Cells<R> &C, int sub, int last, int step_end, hipStream_t s)
 {
+    if (dem_subcycle_single(D)) {
+        if (D.pt.np > 0)
+            hipLaunchKernelGGL(k_dem_subcycle<R>, dim3(1), dim3((unsigned)((D.pt.np + 63) / 64 * 64)), 0, s, D, C,
+                               sub_flags(D, 1, step_end));
+        return;
+    }
     launch_dem<R, true>(D, C, sub_flags(D, last, step_end), sub & 1, s);
 }
 bool dem_sorts_lengths(const Desc &D) { return sort_lengths(D); }
