@@ -70,7 +70,7 @@ struct lbdem_domain {
     // cell arrays (one of the two precisions is used)
     void *df[2] = {nullptr, nullptr};
     int cur = 0;
-    void *drho = nullptr, *j = nullptr, *uprev = nullptr, *un = nullptr, *dudt = nullptr, *gradp = nullptr;
+    void *j = nullptr, *uprev = nullptr, *dudt = nullptr, *gradp = nullptr;
     void *epsp = nullptr, *fam = nullptr, *uf = nullptr, *facc = nullptr;
     void *curl = nullptr;       // lift only
     // bins
@@ -173,10 +173,9 @@ struct lbdem_domain {
         Cells<R> C{};
         C.df_src = (R *)df[cur];
         C.df_dst = (R *)df[cur ^ 1];
-        C.drho = (R *)drho;
         C.j = (R *)j;
         C.uprev = (R *)uprev;
-        C.un = (R *)un;
+        C.un = (R *)fam;
         C.dudt = (R *)dudt;
         C.gradp = (R *)gradp;
         C.epsp = (R *)epsp;
@@ -734,37 +733,30 @@ template <typename R>
 void read_field_impl(lbdem_domain_t h, int field, double *dev_out)
 {
     const int64_t nc = h->geo.nc;
-    const R *src = nullptr;
+    const R *src = nullptr, *vec4 = nullptr;
     int ncomp = 1;
     switch (field) {
-    case LBDEM_FIELD_DRHO: {
+    case LBDEM_FIELD_DRHO:
         // moments of the current state
-        Desc D = h->desc();
-        Cells<R> C = h->cells<R>();
-        launch_moments<R>(D, C, h->stream);
-        src = (const R *)h->drho;
-        break;
-    }
-    case LBDEM_FIELD_J: src = (const R *)h->j; ncomp = 3; break;
+        launch_moments<R>(h->desc(), h->cells<R>(), h->stream);
+        launch_vec4_w_to_double<R>((const R *)h->j, dev_out, nc, h->stream);
+        hip_check(hipGetLastError(), "read_field");
+        return;
     case LBDEM_FIELD_EPS_F:
         launch_fluid_fraction<R>((const R *)h->epsp, dev_out, nc, h->stream);
         hip_check(hipGetLastError(), "read_field");
         return;
-    case LBDEM_FIELD_F_ACC: src = (const R *)h->facc; ncomp = 3; break;
-    case LBDEM_FIELD_DUDT:
-        launch_vec4_to_double<R>((const R *)h->dudt, dev_out, nc, h->stream);
-        hip_check(hipGetLastError(), "read_field");
-        return;
-    case LBDEM_FIELD_GRADP: src = (const R *)h->gradp; ncomp = 3; break;
+    case LBDEM_FIELD_J: vec4 = (const R *)h->j; break;
+    case LBDEM_FIELD_F_ACC: vec4 = (const R *)h->facc; break;
+    case LBDEM_FIELD_DUDT: vec4 = (const R *)h->dudt; break;
+    case LBDEM_FIELD_GRADP: vec4 = (const R *)h->gradp; break;
+    case LBDEM_FIELD_CURL: vec4 = (const R *)h->curl; break;
     case LBDEM_FIELD_UPREV: src = (const R *)h->uprev; ncomp = 3; break;
     case LBDEM_FIELD_PDF: src = (const R *)h->df[h->cur]; ncomp = 19; break;
-    case LBDEM_FIELD_CURL:
-        launch_vec4_to_double<R>((const R *)h->curl, dev_out, nc, h->stream);
-        hip_check(hipGetLastError(), "read_field");
-        return;
     default: throw std::runtime_error("unknown field id");
     }
-    launch_to_double<R>(src, dev_out, ncomp * nc, h->stream);
+    if (vec4) launch_vec4_to_double<R>(vec4, dev_out, nc, h->stream);
+    else launch_to_double<R>(src, dev_out, ncomp * nc, h->stream);
     hip_check(hipGetLastError(), "read_field");
 }
 
@@ -876,19 +868,12 @@ lbdem_status lbdem_create(const lbdem_params *p, void *hip_stream, lbdem_domain_
         const size_t rs = h->rsize();
         h->df[0] = h->dalloc(rs * 19 * nc);
         h->df[1] = h->dalloc(rs * 19 * nc);
-        h->drho = h->dalloc(rs * nc);
-        h->j = h->dalloc(rs * 3 * nc);
         h->uprev = h->dalloc(rs * 3 * nc);
-        h->un = h->dalloc(rs * 3 * nc);
-        h->dudt = h->dalloc(rs * 4 * nc);
-        h->gradp = h->dalloc(rs * 3 * nc);
         h->epsp = h->dalloc(rs * nc);
-        h->fam = h->dalloc(rs * 3 * nc);
-        h->uf = h->dalloc(rs * 3 * nc);
-        h->facc = h->dalloc(rs * 3 * nc);
-        if (h->phys.use_lift) {
-            h->curl = h->dalloc(rs * 4 * nc);
-            hip_check(hipMemsetAsync(h->curl, 0, rs * 4 * nc, h->stream), "memset");
+        for (void **q : {&h->j, &h->dudt, &h->gradp, &h->fam, &h->uf, &h->facc, &h->curl}) {
+            if (q == &h->curl && !h->phys.use_lift) continue;
+            *q = h->dalloc(rs * 4 * nc);
+            hip_check(hipMemsetAsync(*q, 0, rs * 4 * nc, h->stream), "memset");
         }
         h->cnt = (int *)h->dalloc(sizeof(int) * nc);
         h->start = (int *)h->dalloc(sizeof(int) * (nc + 1));
@@ -901,10 +886,8 @@ lbdem_status lbdem_create(const lbdem_params *p, void *hip_stream, lbdem_domain_
         h->diag_part = (double *)h->dalloc(sizeof(double) * 12 * 1024);
         h->diag_out = (double *)h->dalloc(sizeof(double) * 16);
         for (void *q : {h->df[0], h->df[1]}) hip_check(hipMemsetAsync(q, 0, rs * 19 * nc, h->stream), "memset");
-        for (void *q : {h->drho, h->epsp}) hip_check(hipMemsetAsync(q, 0, rs * nc, h->stream), "memset");
-        for (void *q : {h->j, h->uprev, h->un, h->gradp, h->fam, h->uf, h->facc})
-            hip_check(hipMemsetAsync(q, 0, rs * 3 * nc, h->stream), "memset");
-        hip_check(hipMemsetAsync(h->dudt, 0, rs * 4 * nc, h->stream), "memset");
+        hip_check(hipMemsetAsync(h->epsp, 0, rs * nc, h->stream), "memset");
+        hip_check(hipMemsetAsync(h->uprev, 0, rs * 3 * nc, h->stream), "memset");
         hip_check(hipMemsetAsync(h->cnt, 0, sizeof(int) * nc, h->stream), "memset");
         hip_check(hipMemsetAsync(h->start, 0, sizeof(int) * (nc + 1), h->stream), "memset");
         hip_check(hipMemsetAsync(h->flags, 0, sizeof(int) * 4, h->stream), "memset");

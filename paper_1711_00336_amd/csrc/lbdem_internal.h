@@ -37,21 +37,23 @@ struct Phys {
     int rbin;                   // DEM search radius in cells (list build)
 };
 
-// Cell fields, [ncomp][nc] each. R = float (FP32 deviations) or double.
+// Cell fields, [ncomp][nc] or, where a pass reads the vector of one cell (or of a
+// neighbour) whole, [nc][4] with a scalar that is read beside it.
+// R = float (FP32 deviations) or double.
 template <typename R>
 struct Cells {
     R *df_src, *df_dst;         // [19][nc] f_q - w_q
-    R *drho;                    // rho - 1 at step start
-    R *j;                       // [3] sum_q c_q f_q at step start
-    R *uprev;                   // [3] u_f of the previous step
-    R *un;                      // [3] u_f of the current post-stream state
-    R *dudt;                    // [nc][4] Du_f/Dt as (x, y, z, 0) per cell
-    R *gradp;                   // [3] grad P
-    R *epsp;                    // solid fraction 1 - eps_f of the current positions
-    R *fam;                     // [3] -sum_p D F_am of the current subcycle
-    R *uf;                      // [3] u_f re-evaluated with f_ext = eps_f f_b + fam
-    R *facc;                    // [3] subcycle mean of f_ext
-    R *curl;                    // [nc][4] curl of u_f at the subcycle start as (x, y, z, 0) (lift only)
+    R *j;                       // [nc][4] sum_q c_q f_q, rho - 1 at step start
+    R *uprev;                   // [3][nc] u_f of the previous step
+    R *un;                      // [nc][4] u_f, rho - 1 of the current post-stream state (in fam's memory:
+                                // the cell-field pass has read it before the first spreading writes fam)
+    R *dudt;                    // [nc][4] Du_f/Dt, 0
+    R *gradp;                   // [nc][4] grad P, 0
+    R *epsp;                    // [nc] solid fraction 1 - eps_f of the current positions
+    R *fam;                     // [nc][4] -sum_p D F_am of the current subcycle, its eps_p
+    R *uf;                      // [nc][4] u_f re-evaluated with f_ext = eps_f f_b + fam, its eps_p
+    R *facc;                    // [nc][4] subcycle mean of f_ext, 0
+    R *curl;                    // [nc][4] curl of u_f at the subcycle start, 0 (lift only)
 };
 
 // 1-cell bins: particles sorted by the cell of their position.
@@ -174,6 +176,7 @@ template <typename R> void launch_stream_collide(const Desc &D, const Cells<R> &
 template <typename R> void launch_zero(R *p, int64_t n, hipStream_t s);
 template <typename R> void launch_to_double(const R *src, double *dst, int64_t n, hipStream_t s);
 template <typename R> void launch_vec4_to_double(const R *src, double *dst, int64_t nc, hipStream_t s);
+template <typename R> void launch_vec4_w_to_double(const R *src, double *dst, int64_t nc, hipStream_t s);
 template <typename R> void launch_fluid_fraction(const R *src, double *dst, int64_t nc, hipStream_t s);
 template <typename R> void launch_from_double(const double *src, R *dst, int64_t n, hipStream_t s);
 template <typename R>

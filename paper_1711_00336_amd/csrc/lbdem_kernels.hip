@@ -160,30 +160,32 @@ __device__ __forceinline__ int64_t particle_cell(const Geo &g, double x, double 
 
 __device__ __forceinline__ double sphere_volume(double d) { return M_PI * d * d * d / 6.0; }
 
-// 4-vector cell fields ([nc][4], components x, y, z, 0): one 16- or 32-byte
-// access per cell instead of three scattered ones
-__device__ __forceinline__ void store_vec4(float *p, float a, float b, float c)
+// 4-vector cell fields ([nc][4], a vector and a scalar that is read with it, or
+// 0): one 16- or 32-byte access per cell instead of three or four scattered ones
+__device__ __forceinline__ void store_vec4(float *p, float a, float b, float c, float d = 0.0f)
 {
-    *reinterpret_cast<float4 *>(p) = make_float4(a, b, c, 0.0f);
+    *reinterpret_cast<float4 *>(p) = make_float4(a, b, c, d);
 }
-__device__ __forceinline__ void store_vec4(double *p, double a, double b, double c)
+__device__ __forceinline__ void store_vec4(double *p, double a, double b, double c, double d = 0.0)
 {
     reinterpret_cast<double2 *>(p)[0] = make_double2(a, b);
-    reinterpret_cast<double2 *>(p)[1] = make_double2(c, 0.0);
+    reinterpret_cast<double2 *>(p)[1] = make_double2(c, d);
 }
-__device__ __forceinline__ void load_vec4(const float *p, float v[3])
+__device__ __forceinline__ void load_vec4(const float *p, float v[4])
 {
     const float4 t = *reinterpret_cast<const float4 *>(p);
     v[0] = t.x;
     v[1] = t.y;
     v[2] = t.z;
+    v[3] = t.w;
 }
-__device__ __forceinline__ void load_vec4(const double *p, double v[3])
+__device__ __forceinline__ void load_vec4(const double *p, double v[4])
 {
     const double2 a = reinterpret_cast<const double2 *>(p)[0], b = reinterpret_cast<const double2 *>(p)[1];
     v[0] = a.x;
     v[1] = a.y;
     v[2] = b.x;
+    v[3] = b.y;
 }
 
 // ---------------------------------------------------------------------------
@@ -205,10 +207,7 @@ __global__ __launch_bounds__(kBlock) void k_moments(Desc D, Cells<R> C)
         if (CY(q) > 0) jy += f; else if (CY(q) < 0) jy -= f;
         if (CZ(q) > 0) jz += f; else if (CZ(q) < 0) jz -= f;
     }
-    C.drho[c] = r;
-    C.j[c] = jx;
-    C.j[nc + c] = jy;
-    C.j[2 * nc + c] = jz;
+    store_vec4(C.j + 4 * c, jx, jy, jz, r);
     // fluid-phase velocity with the body force only (Eq. MacVel, u_f = u_bar/eps_f);
     // with lift also the first subcycle's u_f, from which its curl is taken
     const double e = 1.0 - (double)C.epsp[c];
@@ -216,14 +215,8 @@ __global__ __launch_bounds__(kBlock) void k_moments(Desc D, Cells<R> C)
     const R u0 = (R)(((double)jx + 0.5 * e * D.p.fb[0]) / (rho * e));
     const R u1 = (R)(((double)jy + 0.5 * e * D.p.fb[1]) / (rho * e));
     const R u2 = (R)(((double)jz + 0.5 * e * D.p.fb[2]) / (rho * e));
-    C.un[c] = u0;
-    C.un[nc + c] = u1;
-    C.un[2 * nc + c] = u2;
-    if (D.p.use_lift) {
-        C.uf[c] = u0;
-        C.uf[nc + c] = u1;
-        C.uf[2 * nc + c] = u2;
-    }
+    store_vec4(C.un + 4 * c, u0, u1, u2, r);
+    if (D.p.use_lift) store_vec4(C.uf + 4 * c, u0, u1, u2, C.epsp[c]);
 }
 
 // Neighbours x + c_q with the wall ghost rule: the mirrored in-domain cell;
@@ -291,10 +284,9 @@ __global__ __launch_bounds__(kBlock) void k_cellfields(Desc D, Cells<R> C)
     for (int q = 0; q < 19; ++q) {
         double sg;
         const int64_t nb = ghost(h, q, sg);
-        const double u0 = (double)C.un[nb];
-        const double u1 = (double)C.un[nc + nb];
-        const double u2 = (double)C.un[2 * nc + nb];
-        const double dr = (double)C.drho[nb];
+        R v[4];
+        load_vec4(C.un + 4 * nb, v);
+        const double u0 = (double)v[0], u1 = (double)v[1], u2 = (double)v[2], dr = (double)v[3];
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             if (CC(q, a) == 0) continue;
@@ -305,10 +297,9 @@ __global__ __launch_bounds__(kBlock) void k_cellfields(Desc D, Cells<R> C)
             gp[a] += wc * dr;
         }
     }
-    double un[3];
-    un[0] = (double)C.un[c];
-    un[1] = (double)C.un[nc + c];
-    un[2] = (double)C.un[2 * nc + c];
+    R un0[4];
+    load_vec4(C.un + 4 * c, un0);
+    const double un[3] = {(double)un0[0], (double)un0[1], (double)un0[2]};
     const bool have_prev = *D.stepc > 0;
     R du[3];
 #pragma unroll
@@ -318,10 +309,10 @@ __global__ __launch_bounds__(kBlock) void k_cellfields(Desc D, Cells<R> C)
         for (int a = 0; a < 3; ++a) conv += un[a] * (3.0 * G[a][b]);
         const double dtu = have_prev ? (un[b] - (double)C.uprev[b * nc + c]) : 0.0;
         du[b] = (R)(dtu + conv);
-        C.gradp[b * nc + c] = (R)gp[b];
         C.uprev[b * nc + c] = (R)un[b];
-        C.facc[b * nc + c] = (R)0;
     }
+    store_vec4(C.gradp + 4 * c, (R)gp[0], (R)gp[1], (R)gp[2]);
+    store_vec4(C.facc + 4 * c, (R)0, (R)0, (R)0);
     store_vec4(C.dudt + 4 * c, du[0], du[1], du[2]);
 }
 
@@ -349,7 +340,9 @@ __global__ __launch_bounds__(kBlock) void k_curl(Desc D, Cells<R> C)
     for (int q = 1; q < 19; ++q) {
         double sg;
         const int64_t nb = ghost(h, q, sg);
-        const double u0 = sg * (double)C.uf[nb], u1 = sg * (double)C.uf[nc + nb], u2 = sg * (double)C.uf[2 * nc + nb];
+        R v[4];
+        load_vec4(C.uf + 4 * nb, v);
+        const double u0 = sg * (double)v[0], u1 = sg * (double)v[1], u2 = sg * (double)v[2];
         s[0] += WQ(q) * (CY(q) * u2 - CZ(q) * u1);
         s[1] += WQ(q) * (CZ(q) * u0 - CX(q) * u2);
         s[2] += WQ(q) * (CX(q) * u1 - CY(q) * u0);
@@ -473,7 +466,7 @@ __device__ __forceinline__ void interp_dudt(const Desc &D, const Cells<R> &C, co
                 const int cx = stencil_coord(st.b[0], ox - 1, D.g.n[0], D.g.per[0]);
                 const int64_t cell = cidx(D.g, cx, cy, cz);
                 const R w = (R)(st.w[0][ox] * st.w[1][oy] * sel3(st.w[2], oz));
-                R v[3];
+                R v[4];
                 load_vec4(C.dudt + 4 * cell, v);
 #pragma unroll
                 for (int b = 0; b < 3; ++b) Du[b] += w * v[b];
@@ -514,7 +507,6 @@ __global__ __launch_bounds__(kBlock) void k_part_am(Desc D, Cells<R> C)
     const int64_t i = gidx();
     const Parts &P = D.pt;
     if (i >= P.np) return;
-    const int64_t nc = D.g.nc;
     Stencil st;
     load_stencil<R>(P, i, st);
     R Du[3] = {(R)0, (R)0, (R)0};
@@ -535,16 +527,17 @@ __global__ __launch_bounds__(kBlock) void k_part_am(Desc D, Cells<R> C)
                 const int cx = stencil_coord(st.b[0], ox - 1, D.g.n[0], D.g.per[0]);
                 const int64_t cell = cidx(D.g, cx, cy, cz);
                 const R w = (R)(st.w[0][ox] * st.w[1][oy] * sel3(st.w[2], oz));
-                R v[3];
+                R v[4];
                 load_vec4(C.dudt + 4 * cell, v);
 #pragma unroll
                 for (int b = 0; b < 3; ++b) Du[b] += w * v[b];
                 if (LIFT) {
-                    R o[3];
+                    R o[4], uf[4];
                     load_vec4(C.curl + 4 * cell, o);
+                    load_vec4(C.uf + 4 * cell, uf);
 #pragma unroll
                     for (int b = 0; b < 3; ++b) {
-                        U[b] += w * C.uf[b * nc + cell];
+                        U[b] += w * uf[b];
                         Om[b] += w * o[b];
                     }
                 }
@@ -677,49 +670,59 @@ __device__ __forceinline__ void gather_value(const Parts &P, int p, double *v)
     }
 }
 
+// fam = -sam and u_f = (j + (eps_f f_b + fam)/2) / (rho eps_f) of cell c with the
+// solid fraction ep; both keep the solid fraction for the passes that read them
 template <typename R>
-__device__ __forceinline__ void store_fam_uf(const Desc &D, const Cells<R> &C, int64_t c, double e, const double *sam)
+__device__ __forceinline__ void store_fam_uf(const Desc &D, const Cells<R> &C, int64_t c, R ep, const double *sam)
 {
-    const int64_t nc = D.g.nc;
-    const double rho = 1.0 + (double)C.drho[c];
+    R j[4], fam[3], uf[3];
+    load_vec4(C.j + 4 * c, j);
+    const double e = 1.0 - (double)ep;
+    const double rho = 1.0 + (double)j[3];
 #pragma unroll
     for (int b = 0; b < 3; ++b) {
-        const R fam = (R)(-sam[b]);
-        C.fam[b * nc + c] = fam;
-        const double fext = e * D.p.fb[b] + (double)fam;
-        C.uf[b * nc + c] = (R)(((double)C.j[b * nc + c] + 0.5 * fext) / (rho * e));
+        fam[b] = (R)(-sam[b]);
+        const double fext = e * D.p.fb[b] + (double)fam[b];
+        uf[b] = (R)(((double)j[b] + 0.5 * fext) / (rho * e));
     }
+    store_vec4(C.fam + 4 * c, fam[0], fam[1], fam[2], ep);
+    store_vec4(C.uf + 4 * c, uf[0], uf[1], uf[2], ep);
 }
 
 template <typename R, int MODE>
 __device__ __forceinline__ void gather_store(const Desc &D, const Cells<R> &C, int64_t c, const double *s)
 {
-    const int64_t nc = D.g.nc;
     if (MODE == MODE_AM) {
-        store_fam_uf<R>(D, C, c, 1.0 - (double)C.epsp[c], s);
+        store_fam_uf<R>(D, C, c, C.epsp[c], s);
     } else if (MODE == MODE_EPS_AM) {
         const double e = 1.0 - s[0];
         if (!(e > 0.0) || !isfinite(e)) atomicOr(D.flags, FLAG_EPS);
         C.epsp[c] = (R)s[0];
-        store_fam_uf<R>(D, C, c, 1.0 - (double)(R)s[0], s + 1);
+        store_fam_uf<R>(D, C, c, (R)s[0], s + 1);
     } else if (MODE == MODE_FD) {
-        const double e = 1.0 - (double)C.epsp[c];
+        R fam[4], facc[4];
+        load_vec4(C.fam + 4 * c, fam);
+        load_vec4(C.facc + 4 * c, facc);
+        const double e = 1.0 - (double)fam[3];
 #pragma unroll
         for (int b = 0; b < 3; ++b) {
-            const double fext = e * D.p.fb[b] + (double)C.fam[b * nc + c] - s[b];
-            C.facc[b * nc + c] = (R)((double)C.facc[b * nc + c] + fext * D.p.dt_int);
+            const double fext = e * D.p.fb[b] + (double)fam[b] - s[b];
+            facc[b] = (R)((double)facc[b] + fext * D.p.dt_int);
         }
+        store_vec4(C.facc + 4 * c, facc[0], facc[1], facc[2]);
         if (c == 0) D.pt.need[0] = 0;  // the list build of this subcycle is done, its last substep not yet begun
     } else {
         const double e = 1.0 - s[0];
         if (!(e > 0.0) || !isfinite(e)) atomicOr(D.flags, FLAG_EPS);
         C.epsp[c] = (R)s[0];
         if (MODE == MODE_EPS_UF) {
+            R j[4], uf[3];
+            load_vec4(C.j + 4 * c, j);
             const double ef = 1.0 - (double)(R)s[0];
-            const double rho = 1.0 + (double)C.drho[c];
+            const double rho = 1.0 + (double)j[3];
 #pragma unroll
-            for (int b = 0; b < 3; ++b)
-                C.uf[b * nc + c] = (R)(((double)C.j[b * nc + c] + 0.5 * ef * D.p.fb[b]) / (rho * ef));
+            for (int b = 0; b < 3; ++b) uf[b] = (R)(((double)j[b] + 0.5 * ef * D.p.fb[b]) / (rho * ef));
+            store_vec4(C.uf + 4 * c, uf[0], uf[1], uf[2], (R)s[0]);
         }
     }
 }
@@ -949,7 +952,7 @@ __device__ __forceinline__ void drag_forces(const Desc &D, int64_t i, const R uf
     const R Re = ((R)1 - ep) * rho_f * d * wn / mu;
     const R fac = (R)3 * (R)M_PI * d * mu * drag_factor(Re, ep);
     const R rp = (R)P.rho[i];
-    const int pid = P.id[i];
+    const int pid = record ? P.id[i] : 0;
 #pragma unroll
     for (int b = 0; b < 3; ++b) {
         const R Fpr = -V * gp[b];
@@ -978,7 +981,6 @@ __global__ __launch_bounds__(kBlock) void k_part_drag(Desc D, Cells<R> C, int re
     const int64_t i = gidx();
     const Parts &P = D.pt;
     if (i >= P.np) return;
-    const int64_t nc = D.g.nc;
     Stencil st;
     load_stencil<R>(P, i, st);
     R uf[3] = {(R)0, (R)0, (R)0}, gp[3] = {(R)0, (R)0, (R)0}, ep = (R)0;
@@ -993,12 +995,15 @@ __global__ __launch_bounds__(kBlock) void k_part_drag(Desc D, Cells<R> C, int re
                 const int cx = stencil_coord(st.b[0], ox - 1, D.g.n[0], D.g.per[0]);
                 const int64_t cell = cidx(D.g, cx, cy, cz);
                 const R w = (R)(st.w[0][ox] * st.w[1][oy] * sel3(st.w[2], oz));
+                R u4[4], g4[4];
+                load_vec4(C.uf + 4 * cell, u4);
+                load_vec4(C.gradp + 4 * cell, g4);
 #pragma unroll
                 for (int b = 0; b < 3; ++b) {
-                    uf[b] += w * C.uf[b * nc + cell];
-                    gp[b] += w * C.gradp[b * nc + cell];
+                    uf[b] += w * u4[b];
+                    gp[b] += w * g4[b];
                 }
-                ep += w * C.epsp[cell];
+                ep += w * u4[3];
             }
         }
     }
@@ -1015,22 +1020,24 @@ __global__ __launch_bounds__(kBlock) void k_part_drag(Desc D, Cells<R> C, int re
 // every particle interpolates from LDS. The arithmetic and its order are
 // those of k_part_am / k_part_drag, so the results are bit-identical.
 // ---------------------------------------------------------------------------
-enum { PASS_AM = 0, PASS_DRAG = 1, PASS_AML = 2 };
+//
+// The cell fields come as 4-vectors, (u_f, eps_p) and grad P for the drag, Du/Dt,
+// u_f and the curl for the added mass with lift: two or three 16-byte accesses
+// per cell, from memory and from LDS, instead of seven or nine 4-byte ones.
+enum { PASS_DRAG = 1, PASS_AML = 2 };
 
-template <typename R, int PASS, int TX, int TY, int TZ>
-__global__ __launch_bounds__(256) void k_part_tile(Desc D, Cells<R> C, int record)
+template <typename R, int PASS, int TX, int TY, int TZ, int NT>
+__global__ __launch_bounds__(NT) void k_part_tile(Desc D, Cells<R> C, int record)
 {
     constexpr int HX = TX + 2, HY = TY + 2, HZ = TZ + 2, NHC = HX * HY * HZ;
-    // Du/Dt | u_f, grad P, eps_p | Du/Dt, u_f, curl u_f
-    constexpr int NV = PASS == PASS_AM ? 3 : (PASS == PASS_DRAG ? 7 : 9);
+    constexpr int NF = PASS == PASS_DRAG ? 2 : 3;  // 4-vectors per cell
     constexpr int NR = TY * TZ;
     static_assert(NR <= 64, "rows of one tile are scanned by one wavefront");
-    __shared__ R cv[NV][NHC];
+    __shared__ __align__(16) R cv[NF][NHC][4];
     __shared__ int rp[NR + 1], rsrc[NR];
 
     const int tid = threadIdx.x;
     const int n0 = D.g.n[0], n1 = D.g.n[1], n2 = D.g.n[2];
-    const int64_t nc = D.g.nc;
     const uint32_t lin = xcd_remap(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z),
                                    gridDim.x * gridDim.y * gridDim.z);
     const int bx = (int)(lin % gridDim.x), by = (int)((lin / gridDim.x) % gridDim.y),
@@ -1059,42 +1066,37 @@ __global__ __launch_bounds__(256) void k_part_tile(Desc D, Cells<R> C, int recor
         if (tid < NR) rp[tid] = incl - cnt;
         if (tid == NR - 1) rp[NR] = incl;
     }
+    // where most tiles are empty, they end before reading their cells
+    if (D.pt.np < (int64_t)gridDim.x * gridDim.y * gridDim.z) {
+        __syncthreads();
+        if (rp[NR] == 0) return;
+    }
     // halo cell fields
-    for (int hc = tid; hc < NHC; hc += 256) {
+    const R *field[3] = {PASS == PASS_DRAG ? C.uf : C.dudt, PASS == PASS_DRAG ? C.gradp : C.uf, C.curl};
+    for (int hc = tid; hc < NHC; hc += NT) {
         const int hx = hc % HX, hy = (hc / HX) % HY, hz = hc / (HX * HY);
-        R v[NV];
+        R v[NF][4];
         if (hx <= lx && hy <= ly && hz <= lz) {
             const int gx = stencil_coord(x0, hx - 1, n0, D.g.per[0]);
             const int gy = stencil_coord(y0, hy - 1, n1, D.g.per[1]);
             const int gz = stencil_coord(z0, hz - 1, n2, D.g.per[2]);
             const int64_t cell = cidx(D.g, gx, gy, gz);
-            if (PASS == PASS_AM) {
-                load_vec4(C.dudt + 4 * cell, v);
-            } else if (PASS == PASS_AML) {
-                load_vec4(C.dudt + 4 * cell, v);
 #pragma unroll
-                for (int b = 0; b < 3; ++b) v[3 + b] = C.uf[b * nc + cell];
-                load_vec4(C.curl + 4 * cell, v + 6);
-            } else {
-#pragma unroll
-                for (int b = 0; b < 3; ++b) {
-                    v[b] = C.uf[b * nc + cell];
-                    v[3 + b] = C.gradp[b * nc + cell];
-                }
-                v[6] = C.epsp[cell];
-            }
+            for (int f = 0; f < NF; ++f) load_vec4(field[f] + 4 * cell, v[f]);
         } else {
 #pragma unroll
-            for (int t = 0; t < NV; ++t) v[t] = (R)0;
+            for (int f = 0; f < NF; ++f)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) v[f][t] = (R)0;
         }
 #pragma unroll
-        for (int t = 0; t < NV; ++t) cv[t][hc] = v[t];
+        for (int f = 0; f < NF; ++f) store_vec4(cv[f][hc], v[f][0], v[f][1], v[f][2], v[f][3]);
     }
     __syncthreads();
 
     const Parts &P = D.pt;
     const int K = rp[NR];
-    for (int k = tid; k < K; k += 256) {
+    for (int k = tid; k < K; k += NT) {
         int lo = 0, hi = NR - 1;
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
@@ -1109,9 +1111,11 @@ __global__ __launch_bounds__(256) void k_part_tile(Desc D, Cells<R> C, int recor
         // having left the domain
         const int hx0 = min(max(st.b[0] - x0, 0), TX - 1), hy0 = min(max(st.b[1] - y0, 0), TY - 1),
                   hz0 = min(max(st.b[2] - z0, 0), TZ - 1);
-        R acc[NV];
+        R acc[NF][4];
 #pragma unroll
-        for (int t = 0; t < NV; ++t) acc[t] = (R)0;
+        for (int f = 0; f < NF; ++f)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) acc[f][t] = (R)0;
 #pragma unroll 1
         for (int oz = 0; oz < 3; ++oz) {
 #pragma unroll
@@ -1120,34 +1124,21 @@ __global__ __launch_bounds__(256) void k_part_tile(Desc D, Cells<R> C, int recor
                 for (int ox = 0; ox < 3; ++ox) {
                     const int hc = ((hz0 + oz) * HY + (hy0 + oy)) * HX + (hx0 + ox);
                     const R w = (R)(st.w[0][ox] * st.w[1][oy] * sel3(st.w[2], oz));
-                    if (PASS == PASS_AM) {
 #pragma unroll
-                        for (int b = 0; b < 3; ++b) acc[b] += w * cv[b][hc];
-                    } else if (PASS == PASS_AML) {
+                    for (int f = 0; f < NF; ++f) {
+                        R v[4];
+                        load_vec4(cv[f][hc], v);
 #pragma unroll
-                        for (int b = 0; b < 3; ++b) {
-                            acc[b] += w * cv[b][hc];
-                            acc[3 + b] += w * cv[3 + b][hc];
-                            acc[6 + b] += w * cv[6 + b][hc];
-                        }
-                    } else {
-#pragma unroll
-                        for (int b = 0; b < 3; ++b) {
-                            acc[b] += w * cv[b][hc];
-                            acc[3 + b] += w * cv[3 + b][hc];
-                        }
-                        acc[6] += w * cv[6][hc];
+                        for (int t = 0; t < (PASS == PASS_DRAG && f == 0 ? 4 : 3); ++t) acc[f][t] += w * v[t];
                     }
                 }
             }
         }
-        if (PASS == PASS_AM) {
-            am_force<R>(D, i, acc);
-        } else if (PASS == PASS_AML) {
-            am_force<R>(D, i, acc);
-            lift_force<R>(D, i, acc + 3, acc + 6);
+        if (PASS == PASS_AML) {
+            am_force<R>(D, i, acc[0]);
+            lift_force<R>(D, i, acc[1], acc[NF - 1]);
         } else {
-            drag_forces<R>(D, i, acc, acc + 3, acc[6], record);
+            drag_forces<R>(D, i, acc[0], acc[1], acc[0][3], record);
         }
     }
 }
@@ -2381,7 +2372,9 @@ __device__ __forceinline__ void collide_cell(const Desc &D, const Cells<R> &C, i
     }
     const R one = (R)1;
     const R rho = one + r;
-    const R fx = C.facc[c], fy = C.facc[nc + c], fz = C.facc[2 * nc + c];
+    R fa[4];
+    load_vec4(C.facc + 4 * c, fa);
+    const R fx = fa[0], fy = fa[1], fz = fa[2];
     const R half = (R)0.5;
     const R ux = (jx + half * fx) / rho, uy = (jy + half * fy) / rho, uz = (jz + half * fz) / rho;
     const R eps = one - C.epsp[c];
@@ -2597,6 +2590,13 @@ __global__ __launch_bounds__(kBlock) void k_pack_vec(const double *src, int64_t 
     for (int a = 0; a < 3; ++a) out[3 * i + a] = src[a * cap + i];
 }
 
+// component w of [nc][4]
+template <typename A> __global__ void k_vec4_w(const A *src, double *dst, int64_t nc)
+{
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < nc; c += stride) dst[c] = (double)src[4 * c + 3];
+}
+
 __global__ void k_set_step(long long *s, long long v) { *s = v; }
 __global__ void k_set_int(int *p, int v) { *p = v; }
 
@@ -2655,7 +2655,7 @@ template <typename R> void launch_part_am(const Desc &D, const Cells<R> &C, hipS
     }
     constexpr int TZ = sizeof(R) == 4 ? 8 : 4;
     dim3 grid((D.g.n[0] + 15) / 16, (D.g.n[1] + 3) / 4, (D.g.n[2] + TZ - 1) / TZ);
-    hipLaunchKernelGGL((k_part_tile<R, PASS_AML, 16, 4, TZ>), grid, dim3(256), 0, s, D, C, 0);
+    hipLaunchKernelGGL((k_part_tile<R, PASS_AML, 16, 4, TZ, 256>), grid, dim3(256), 0, s, D, C, 0);
 }
 // gather variants (chosen per domain by the autotuner, else by particle
 // density): 0 tiles of 16x4x8 cells (two per thread, up to 256 staged
@@ -2702,12 +2702,19 @@ template <typename R> void launch_part_drag(const Desc &D, const Cells<R> &C, in
         hipLaunchKernelGGL(k_part_drag<R>, dim3(nblocks(D.pt.np)), dim3(kBlock), 0, s, D, C, record);
         return;
     }
-    // FP32: tiles of 16x8x8 cells (a halo of 1.76 cells per owned cell
-    // against 2.1 for 16x4x8; 67 vs 71.5 us on the dilute workload); FP64
-    // keeps 16x4x8, whose 7 staged fields stay within 64 KiB of LDS
-    constexpr int TY = sizeof(R) == 4 ? 8 : 4;
-    dim3 grid((D.g.n[0] + 15) / 16, (D.g.n[1] + TY - 1) / TY, (D.g.n[2] + 7) / 8);
-    hipLaunchKernelGGL((k_part_tile<R, PASS_DRAG, 16, TY, 8>), grid, dim3(256), 0, s, D, C, record);
+    const auto tiles = [&](int ty, int tz) {
+        return dim3((D.g.n[0] + 15) / 16, (D.g.n[1] + ty - 1) / ty, (D.g.n[2] + tz - 1) / tz);
+    };
+    // FP32, 2^19 cells and more: tiles of 16x8x8 cells (a halo of 1.76 cells per
+    // owned cell, 58 KB), which below that leave CUs without a tile; 16x4x4 there
+    // (2.53, 21 KB) and in the FP64 form (41 KB). A coupled step, 16x8x8 / 16x4x4:
+    // 128^3 3.07 / 3.15 ms, 97x90x101 3.69 / 3.68, batch of 12 boxes of 17^3 to 46^3
+    // 5.6 / 5.1.
+    if (sizeof(R) == 4 && D.g.nc >= (int64_t)1 << 19)
+        hipLaunchKernelGGL((k_part_tile<R, PASS_DRAG, 16, sizeof(R) == 4 ? 8 : 4, sizeof(R) == 4 ? 8 : 4, 512>),
+                           tiles(8, 8), dim3(512), 0, s, D, C, record);
+    else
+        hipLaunchKernelGGL((k_part_tile<R, PASS_DRAG, 16, 4, 4, 256>), tiles(4, 4), dim3(256), 0, s, D, C, record);
 }
 template <typename R> void launch_gather_fd(const Desc &D, const Cells<R> &C, hipStream_t s)
 {
@@ -2754,6 +2761,10 @@ template <typename R> void launch_vec4_to_double(const R *src, double *dst, int6
 {
     if (nc > 0)
         hipLaunchKernelGGL((k_vec4_to_soa<R>), dim3(grid_stride_blocks(nc)), dim3(kBlock), 0, s, src, dst, nc);
+}
+template <typename R> void launch_vec4_w_to_double(const R *src, double *dst, int64_t nc, hipStream_t s)
+{
+    if (nc > 0) hipLaunchKernelGGL((k_vec4_w<R>), dim3(grid_stride_blocks(nc)), dim3(kBlock), 0, s, src, dst, nc);
 }
 template <typename R> void launch_to_double(const R *src, double *dst, int64_t n, hipStream_t s)
 {
@@ -2940,6 +2951,7 @@ void launch_set_step(long long *stepc, long long v, hipStream_t s)
     template void launch_zero<R>(R *, int64_t, hipStream_t);                                                \
     template void launch_to_double<R>(const R *, double *, int64_t, hipStream_t);                          \
     template void launch_vec4_to_double<R>(const R *, double *, int64_t, hipStream_t);                     \
+    template void launch_vec4_w_to_double<R>(const R *, double *, int64_t, hipStream_t);                   \
     template void launch_fluid_fraction<R>(const R *, double *, int64_t, hipStream_t);                     \
     template void launch_from_double<R>(const double *, R *, int64_t, hipStream_t);                        \
     template void launch_diag<R>(const Desc &, const Cells<R> &, const R *, double *, int, double *, hipStream_t);
