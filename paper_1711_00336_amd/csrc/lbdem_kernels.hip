@@ -2707,14 +2707,20 @@ template <typename R> void launch_part_drag(const Desc &D, const Cells<R> &C, in
     };
     // FP32, 2^19 cells and more: tiles of 16x8x8 cells (a halo of 1.76 cells per
     // owned cell, 58 KB), which below that leave CUs without a tile; 16x4x4 there
-    // (2.53, 21 KB) and in the FP64 form (41 KB). A coupled step, 16x8x8 / 16x4x4:
-    // 128^3 3.07 / 3.15 ms, 97x90x101 3.69 / 3.68, batch of 12 boxes of 17^3 to 46^3
-    // 5.6 / 5.1.
+    // (2.53, 21 KB). A coupled step, 16x8x8 / 16x4x4: 128^3 3.07 / 3.15 ms, 97x90x101
+    // 3.69 / 3.68, batch of 12 boxes of 17^3 to 46^3 5.6 / 5.1. FP64: 16x4x4 (41 KB)
+    // as long as all tiles are resident at once (3 on each of 256 CUs), else 16x4x8
+    // (2.11, 69 KB): 61x53x71 12.6 us against 17.4, 16^3 and 32x32x64 1 to 3 % of a
+    // step faster with 16x4x4.
+    const dim3 small = tiles(4, 4);
     if (sizeof(R) == 4 && D.g.nc >= (int64_t)1 << 19)
         hipLaunchKernelGGL((k_part_tile<R, PASS_DRAG, 16, sizeof(R) == 4 ? 8 : 4, sizeof(R) == 4 ? 8 : 4, 512>),
                            tiles(8, 8), dim3(512), 0, s, D, C, record);
+    else if (sizeof(R) == 8 && (int64_t)small.x * small.y * small.z > 3 * 256)
+        hipLaunchKernelGGL((k_part_tile<R, PASS_DRAG, 16, 4, sizeof(R) == 8 ? 8 : 4, 256>), tiles(4, 8), dim3(256), 0, s,
+                           D, C, record);
     else
-        hipLaunchKernelGGL((k_part_tile<R, PASS_DRAG, 16, 4, 4, 256>), tiles(4, 4), dim3(256), 0, s, D, C, record);
+        hipLaunchKernelGGL((k_part_tile<R, PASS_DRAG, 16, 4, 4, 256>), small, dim3(256), 0, s, D, C, record);
 }
 template <typename R> void launch_gather_fd(const Desc &D, const Cells<R> &C, hipStream_t s)
 {
