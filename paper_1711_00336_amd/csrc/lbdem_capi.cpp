@@ -157,7 +157,7 @@ struct lbdem_domain {
         D.g = geo;
         D.p = phys;
         D.t = tune;
-        D.b = Bins{cnt, start, list, bsum, loc};
+        D.b = Bins{cnt, start, list, bsum, loc, flags + 1};
         D.pt = pt;
         D.o = ord;
         // default: the blocked order once the particles outgrow an XCD's cache

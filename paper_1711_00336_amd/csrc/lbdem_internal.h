@@ -63,6 +63,7 @@ struct Bins {
     int *list;                  // [np] slots, ordered by (cell, id)
     int *bsum;                  // scan block sums (exclusive prefix after the top-level scan)
     int *loc;                   // [nc] prefix of cnt within its scan block
+    int *done;                  // scan blocks that have written their sum (0 between scans)
 };
 
 // Packed copy of what a DEM pair evaluation reads of a particle, one record per
