@@ -403,7 +403,7 @@ void rebuild_particle_fields(lbdem_domain_t h)
     launch_bin_build(h->desc(), h->stream);
     launch_reorder(h->desc(), h->stream);
     if (dem_sorts_lengths(h->desc())) {  // once more with the lengths known
-        launch_nlist(h->desc(), 0, h->stream);
+        launch_nlist<R>(h->desc(), h->stream);
         launch_reorder(h->desc(), h->stream);
     }
     launch_set_int(h->pt.need + 1, 0, h->stream);
@@ -659,15 +659,17 @@ void enqueue_step(lbdem_domain_t h)
     launch_cls(h, 5, [&] { launch_gather_am<R>(h->desc(), C, s); });
     for (int k = 0; k < nint; ++k) {
         const int last_sub = k == nint - 1;
-        // the lists before the drag spreading, which clears the rebuild request
-        launch_cls(h, 8, [&] { launch_nlist(h->desc(), k == 0, s); });
+        // the lists before the drag spreading, which clears the requests served
+        if (!dem_builds_lists(h->desc())) launch_cls(h, 8, [&] { launch_nlist<R>(h->desc(), s); });
         launch_cls(h, 4, [&] { launch_part_drag<R>(h->desc(), C, last_sub, s); });
-        launch_cls(h, 6, [&] { launch_gather_fd<R>(h->desc(), C, s); });
+        Desc fd = h->desc();
+        fd.clear = dem_served_requests(fd, k);
+        launch_cls(h, 6, [&] { launch_gather_fd<R>(fd, C, s); });
         for (int sub = 0; sub < h->phys.n_dem; ++sub) {
             const int last_dem = sub == h->phys.n_dem - 1;
             if (dem_subcycle_single(h->desc()) && sub > 0) break;  // substep 0 ran them all
             if (dem_substep_fused(h->desc())) {
-                launch_cls(h, 9, [&] { launch_dem_substep_fused<R>(h->desc(), C, sub, last_dem, last_sub, s); });
+                launch_cls(h, 9, [&] { launch_dem_substep_fused<R>(h->desc(), C, k, sub, s); });
             } else {
                 launch_cls(h, 9, [&] { launch_dem_force<R>(h->desc(), C, s); });
                 launch_cls(h, 10, [&] { launch_integrate<R>(h->desc(), C, last_dem, last_sub, s); });
@@ -1288,8 +1290,9 @@ static void reorder_now(lbdem_domain_t h)
 {
     launch_set_int(h->pt.need + 1, 1, h->stream);
     launch_reorder(h->desc(), h->stream);
-    launch_nlist(h->desc(), 1, h->stream);
+    launch_nlist<R>(h->desc(), h->stream);
     launch_set_int(h->pt.need, 0, h->stream);
+    launch_set_int(h->pt.need + 1, 0, h->stream);
     hip_check(hipGetLastError(), "reordering");
 }
 

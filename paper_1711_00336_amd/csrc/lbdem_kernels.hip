@@ -710,7 +710,11 @@ __device__ __forceinline__ void gather_store(const Desc &D, const Cells<R> &C, i
             facc[b] = (R)((double)facc[b] + fext * D.p.dt_int);
         }
         store_vec4(C.facc + 4 * c, facc[0], facc[1], facc[2]);
-        if (c == 0) D.pt.need[0] = 0;  // the list build of this subcycle is done, its last substep not yet begun
+        if (c == 0) {  // requests that have been served, before this subcycle's substeps make new ones
+#pragma unroll
+            for (int t = 0; t < 3; ++t)
+                if (D.clear & (1 << t)) D.pt.need[t] = 0;
+        }
     } else {
         const double e = 1.0 - s[0];
         if (!(e > 0.0) || !isfinite(e)) atomicOr(D.flags, FLAG_EPS);
@@ -1498,121 +1502,150 @@ __device__ __forceinline__ void search_range(int c, int r, int n, int per, int &
     count = hi - lo + 1;
 }
 
-__global__ __launch_bounds__(kBlock) void k_nlist(Desc D, int first)
+// position and diameter from a record
+template <typename R>
+__device__ __forceinline__ void load_sphere(const DemRec<R> *pk, int64_t i, double x[3], double &d)
 {
-    __shared__ int sid[kBlock / 64][kListLds], ssl[kBlock / 64][kListLds];
+    const double2 *q = reinterpret_cast<const double2 *>(pk + i);
+    const double2 a = q[0], b = q[1];
+    x[0] = a.x;
+    x[1] = a.y;
+    x[2] = b.x;
+    d = b.y;
+}
+
+// the list of slot i, by one wavefront; lds: 2 kListLds ints of its own. Positions
+// come from the records pk of the subcycle's start: the state arrays may already
+// hold another workgroup's new ones.
+template <typename R>
+__device__ __forceinline__ void build_list(const Desc &D, const DemRec<R> *pk, int64_t i, int lane, int *lds)
+{
     const Parts &P = D.pt;
-    if (first && blockIdx.x == 0 && threadIdx.x == 0) P.need[1] = 0;
-    if (P.need[0] == 0 || halted(D)) return;
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    int *sid = lds, *ssl = lds + kListLds;
     const int64_t cap = P.cap;
     const double gap = (D.p.use_lub ? fmax(D.p.h_c, 0.0) : 0.0) + D.p.vskin;
     const int r = D.p.rbin, n0 = D.g.n[0];
+    double xi[3], ri;
+    load_sphere(pk, i, xi, ri);
+    ri *= 0.5;
+    int lo[3], ct[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+        search_range(clampi((int)floor(xi[a]), 0, D.g.n[a] - 1), r, D.g.n[a], D.g.per[a], lo[a], ct[a]);
+    // an x-row is one contiguous run of bins, or two where it wraps
+    const int nrun = lo[0] < 0 || lo[0] + ct[0] > n0 ? 2 : 1;
+    const int nseg = nrun * ct[1] * ct[2];
+    const int64_t base = list_base(P, i);
+    int m = 0;
+    for (int g0 = 0; g0 < nseg; g0 += 64) {
+        const int g = g0 + lane;
+        int q0 = 0, cnt = 0;
+        if (g < nseg) {
+            const int half = g % nrun, row = g / nrun;
+            const int y = wrap1(lo[1] + row % ct[1], D.g.n[1]), z = wrap1(lo[2] + row / ct[1], D.g.n[2]);
+            int a = lo[0], b = lo[0] + ct[0];  // bins a..b-1
+            if (nrun == 2) {
+                if (a < 0) { a += n0; b += n0; }
+                if (half) { a = 0; b -= n0; } else b = n0;
+            }
+            q0 = D.b.start[cidx(D.g, a, y, z)];
+            cnt = D.b.start[cidx(D.g, b - 1, y, z) + 1] - q0;
+        }
+        int incl = cnt;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int t = __shfl_up(incl, off, 64);
+            if (lane >= off) incl += t;
+        }
+        const int total = __shfl(incl, 63, 64);
+        for (int k0 = 0; k0 < total; k0 += 64) {
+            const int k = k0 + lane;
+            // the row of candidate k: the number of rows that end at or before it
+            int row = 0;
+#pragma unroll
+            for (int step = 32; step > 0; step >>= 1)
+                if (__shfl(incl, row + step - 1, 64) <= k) row += step;
+            const int q = __shfl(q0, row & 63, 64) + k - (__shfl(incl, row & 63, 64) - __shfl(cnt, row & 63, 64));
+            int j = -1;
+            if (k < total) {
+                j = D.b.list[q];
+                double dx[3], dj;
+                load_sphere(pk, j, dx, dj);
+#pragma unroll
+                for (int a = 0; a < 3; ++a) dx[a] -= xi[a];
+                min_image(D.g, dx);
+                const double reach = ri + 0.5 * dj + gap;
+                if (j == i || dot3(dx, dx) >= reach * reach) j = -1;
+            }
+            const uint64_t acc = __ballot(j >= 0);
+            if (j >= 0) {
+                const int t = m + __popcll(acc & ((1ull << lane) - 1));
+                if (t < kListLds) {
+                    sid[t] = P.id[j];
+                    ssl[t] = j;
+                } else if (t < P.nbr) {
+                    P.nlist[base + 64 * (int64_t)t] = j;
+                }
+            }
+            m += __popcll(acc);
+        }
+    }
+    if (m > P.nbr) {
+        if (lane == 0) atomicOr(D.flags, FLAG_NLIST);
+        m = P.nbr;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (m <= kListLds) {
+        for (int e = lane; e < m; e += 64) {
+            const int key = sid[e];
+            int rank = 0;
+            for (int t = 0; t < m; ++t) rank += sid[t] < key;
+            P.nlist[base + 64 * (int64_t)rank] = ssl[e];
+        }
+    } else if (lane == 0) {
+        for (int t = 0; t < m; ++t) {
+            const int j = t < kListLds ? ssl[t] : P.nlist[base + 64 * (int64_t)t];
+            const int key = P.id[j];
+            int b = t - 1;
+            while (b >= 0 && P.id[P.nlist[base + 64 * (int64_t)b]] > key) {
+                P.nlist[base + 64 * (int64_t)(b + 1)] = P.nlist[base + 64 * (int64_t)b];
+                --b;
+            }
+            P.nlist[base + 64 * (int64_t)(b + 1)] = j;
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (lane == 0) {
+        P.nnb[i] = m;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) P.xbuild[a * cap + i] = xi[a];
+    }
+}
+
+template <typename R> __global__ __launch_bounds__(kBlock) void k_nlist(Desc D)
+{
+    __shared__ int lds[kBlock / 64][2 * kListLds];
+    const Parts &P = D.pt;
+    if (P.need[0] == 0 || halted(D)) return;
+    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
     // a workgroup takes a run of slots, whose candidates it then finds in its cache
     const int64_t per = (P.np + gridDim.x - 1) / gridDim.x, b0 = xcd_remap(blockIdx.x, gridDim.x) * per;
     const int64_t b1 = b0 + per < P.np ? b0 + per : P.np;
-    for (int64_t i = b0 + wv; i < b1; i += kBlock / 64) {
-        const double xi[3] = {P.x[i], P.x[cap + i], P.x[2 * cap + i]};
-        const double ri = 0.5 * P.d[i];
-        int lo[3], ct[3];
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-            search_range(clampi((int)floor(xi[a]), 0, D.g.n[a] - 1), r, D.g.n[a], D.g.per[a], lo[a], ct[a]);
-        // an x-row is one contiguous run of bins, or two where it wraps
-        const int nrun = lo[0] < 0 || lo[0] + ct[0] > n0 ? 2 : 1;
-        const int nseg = nrun * ct[1] * ct[2];
-        const int64_t base = list_base(P, i);
-        int m = 0;
-        for (int g0 = 0; g0 < nseg; g0 += 64) {
-            const int g = g0 + lane;
-            int q0 = 0, cnt = 0;
-            if (g < nseg) {
-                const int half = g % nrun, row = g / nrun;
-                const int y = wrap1(lo[1] + row % ct[1], D.g.n[1]), z = wrap1(lo[2] + row / ct[1], D.g.n[2]);
-                int a = lo[0], b = lo[0] + ct[0];  // bins a..b-1
-                if (nrun == 2) {
-                    if (a < 0) { a += n0; b += n0; }
-                    if (half) { a = 0; b -= n0; } else b = n0;
-                }
-                q0 = D.b.start[cidx(D.g, a, y, z)];
-                cnt = D.b.start[cidx(D.g, b - 1, y, z) + 1] - q0;
-            }
-            int incl = cnt;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const int t = __shfl_up(incl, off, 64);
-                if (lane >= off) incl += t;
-            }
-            const int total = __shfl(incl, 63, 64);
-            for (int k0 = 0; k0 < total; k0 += 64) {
-                const int k = k0 + lane;
-                // the row of candidate k: the number of rows that end at or before it
-                int row = 0;
-#pragma unroll
-                for (int step = 32; step > 0; step >>= 1)
-                    if (__shfl(incl, row + step - 1, 64) <= k) row += step;
-                const int q = __shfl(q0, row & 63, 64) + k - (__shfl(incl, row & 63, 64) - __shfl(cnt, row & 63, 64));
-                int j = -1;
-                if (k < total) {
-                    j = D.b.list[q];
-                    double dx[3] = {P.x[j] - xi[0], P.x[cap + j] - xi[1], P.x[2 * cap + j] - xi[2]};
-                    min_image(D.g, dx);
-                    const double reach = ri + 0.5 * P.d[j] + gap;
-                    if (j == i || dot3(dx, dx) >= reach * reach) j = -1;
-                }
-                const uint64_t acc = __ballot(j >= 0);
-                if (j >= 0) {
-                    const int t = m + __popcll(acc & ((1ull << lane) - 1));
-                    if (t < kListLds) {
-                        sid[wv][t] = P.id[j];
-                        ssl[wv][t] = j;
-                    } else if (t < P.nbr) {
-                        P.nlist[base + 64 * (int64_t)t] = j;
-                    }
-                }
-                m += __popcll(acc);
-            }
-        }
-        if (m > P.nbr) {
-            if (lane == 0) atomicOr(D.flags, FLAG_NLIST);
-            m = P.nbr;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        if (m <= kListLds) {
-            for (int e = lane; e < m; e += 64) {
-                const int key = sid[wv][e];
-                int rank = 0;
-                for (int t = 0; t < m; ++t) rank += sid[wv][t] < key;
-                P.nlist[base + 64 * (int64_t)rank] = ssl[wv][e];
-            }
-        } else if (lane == 0) {
-            for (int t = 0; t < m; ++t) {
-                const int j = t < kListLds ? ssl[wv][t] : P.nlist[base + 64 * (int64_t)t];
-                const int key = P.id[j];
-                int b = t - 1;
-                while (b >= 0 && P.id[P.nlist[base + 64 * (int64_t)b]] > key) {
-                    P.nlist[base + 64 * (int64_t)(b + 1)] = P.nlist[base + 64 * (int64_t)b];
-                    --b;
-                }
-                P.nlist[base + 64 * (int64_t)(b + 1)] = j;
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        if (lane == 0) {
-            P.nnb[i] = m;
-#pragma unroll
-            for (int a = 0; a < 3; ++a) P.xbuild[a * cap + i] = xi[a];
-        }
-    }
+    for (int64_t i = b0 + wv; i < b1; i += kBlock / 64) build_list<R>(D, (const DemRec<R> *)P.pk, i, lane, lds[wv]);
 }
 
 // what the last substep of a subcycle does besides integrating
 enum : int {
     SUB_LAST = 1,  // du_p/dt, kernel stencil of the new position, bin count, list check
     SUB_AM = 2,    // the next subcycle's added-mass force (without lift, except before a step's end)
-    SUB_END = 4    // the last subcycle of a step: ask for a reordering ahead of the next step
+    SUB_END = 4,   // the last subcycle of a step: ask for a reordering ahead of the next step
+    // where the fused pass builds the lists: SUB_REQ2 if the request to read is
+    // need[2] and the one to make need[0] (every second subcycle), SUB_REQ0 the
+    // other way round
+    SUB_REQ0 = 8,
+    SUB_REQ2 = 16
 };
 
 // One semi-implicit Euler substep of particle i (R5: u and omega first,
@@ -1691,7 +1724,7 @@ __device__ __forceinline__ void integrate_particle(const Desc &D, const Cells<R>
     // At a step's end the reordering (and with it the rebuild) is asked for a
     // little earlier, so that rebuilds fall on step starts, after a reordering.
     const double limit = 0.5 * D.p.vskin - D.p.skin;
-    if (moved > limit) P.need[0] = P.need[1] = 1;
+    if (moved > limit) P.need[sub & SUB_REQ0 ? 2 : 0] = P.need[1] = 1;
     else if ((sub & SUB_END) && moved > 0.8 * limit) P.need[1] = 1;
     atomicAdd(&D.b.cnt[particle_cell(D.g, x[0], x[1], x[2])], 1);
     // the stencil of a position outside the domain or not finite is not taken
@@ -1748,6 +1781,8 @@ __device__ __forceinline__ bool dem_pair(const Desc &D, const PV &pi, const PV &
 }
 
 constexpr int kRun = 2;  // entries per lane and run, several lanes per particle
+constexpr int kDemLds = 4096;  // bytes of LDS per wavefront: 64 records' pieces, a run's terms or a list being built
+static_assert(2 * kListLds * sizeof(int) <= kDemLds && 64 * 4 * sizeof(uint4) <= kDemLds, "");
 
 // one lane per particle: the slots of entry t of four groups of 16 lists, and the
 // calling lane's piece q of those four records (see below)
@@ -1778,8 +1813,8 @@ __device__ __forceinline__ void load_pieces(const DemRec<R> *src, uint32_t q16, 
 }
 
 template <typename R, int G, typename Off>
-__device__ __forceinline__ void dem_particle(const Desc &D, const DemRec<R> *src, int64_t i, int l, PV &pi,
-                                             double Fs[3], double Tq[3])
+__device__ __forceinline__ void dem_particle(const Desc &D, const DemRec<R> *src, int64_t i, int l, char *lds,
+                                             PV &pi, double Fs[3], double Tq[3])
 {
     constexpr int kPieces = rec_pieces<R>();
     const Parts &P = D.pt;
@@ -1815,8 +1850,7 @@ __device__ __forceinline__ void dem_particle(const Desc &D, const DemRec<R> *src
         // which keeps the 16 lanes of one LDS access on different banks. The
         // pieces of the next entry and the slots of the one after are in flight
         // while an entry is evaluated.
-        __shared__ uint4 stage[kBlock / 64][64 * 4];
-        uint4 *T = stage[threadIdx.x >> 6];
+        uint4 *T = (uint4 *)lds;
         const int lane = threadIdx.x & 63, r0 = lane >> 2, q = lane & 3;
         // (the wavefront's lists start at a uniform address)
         const int64_t wave = __builtin_amdgcn_readfirstlane((int)(i >> 6));
@@ -1876,8 +1910,8 @@ __device__ __forceinline__ void dem_particle(const Desc &D, const DemRec<R> *src
         }
     } else {
         constexpr int RS = 3 * 64 + 2;  // stride of one round, keeping the components on other banks
-        __shared__ double terms[kBlock / 64][kRun * RS];
-        double *T = terms[threadIdx.x >> 6];
+        static_assert(sizeof(double) * kRun * RS <= kDemLds, "terms of a run");
+        double *T = (double *)lds;
         const int lane = threadIdx.x & 63, g0 = lane & ~(G - 1);
         constexpr int NC = (3 + G - 1) / G;
         double sum[NC] = {};  // components l, l + G < 3 of Fl
@@ -1938,13 +1972,32 @@ __device__ __forceinline__ void dem_particle(const Desc &D, const DemRec<R> *src
 // alternate between the two record buffers (odd: from pk2 to pk), reading the
 // records of the substep's start and writing the integrated ones to the other
 // buffer, so that no thread sees another's update.
+// LISTS: where a rebuild is due, a workgroup first builds the lists of its own
+// particles, which nobody else reads (a launch of its own, idle most subcycles,
+// took 4 us of them: 32x32x64 cells with 64 particles, ten steps 4.74 -> 4.50 ms).
+template <typename R>
+__device__ __forceinline__ void dem_lists(const Desc &D, int sub, const DemRec<R> *pk, int64_t i0, int n, char *lds)
+{
+    // (need[] does not change during the pass: the condition is uniform)
+    if (D.pt.need[sub & SUB_REQ2 ? 2 : 0] == 0) return;
+    if (!halted(D))
+        for (int k = threadIdx.x >> 6; k < n && i0 + k < D.pt.np; k += blockDim.x >> 6)
+            build_list<R>(D, pk, i0 + k, threadIdx.x & 63, (int *)lds);
+    __syncthreads();
+}
+
 // (4 waves per SIMD in the FP32 form with one lane per particle, which needs 129
 // registers otherwise)
-template <typename R, int G, bool FUSE, typename Off>
+// (LISTS: the instance that can build lists; the code alone costs the others 1 %)
+template <typename R, int G, bool FUSE, typename Off, bool LISTS>
 __global__ __launch_bounds__(kBlock, sizeof(R) == 4 && G == 1 ? 4 : 1) void k_dem_force(Desc D, Cells<R> C, int sub, int odd)
 {
+    __shared__ __align__(16) char lds[kBlock / 64][kDemLds];
+    char *T = lds[threadIdx.x >> 6];
     const Parts &P = D.pt;
+    DemRec<R> *pk = (DemRec<R> *)P.pk, *pk2 = (DemRec<R> *)P.pk2;
     const int64_t v = gidx();
+    if constexpr (LISTS) dem_lists<R>(D, sub, pk, (v - threadIdx.x) / G, kBlock / G, T);
     int64_t i = v / G;
     const int l = (int)(v % G);
     // a wavefront with particles keeps all its lanes (they load for each other);
@@ -1952,10 +2005,9 @@ __global__ __launch_bounds__(kBlock, sizeof(R) == 4 && G == 1 ? 4 : 1) void k_de
     const bool own = i < P.np;
     if ((v & ~(int64_t)63) / G >= P.np) return;
     if (!own) i = P.np - 1;
-    DemRec<R> *pk = (DemRec<R> *)P.pk, *pk2 = (DemRec<R> *)P.pk2;
     double F[3], Tq[3];
     PV pi;
-    dem_particle<R, G, Off>(D, FUSE && odd ? pk2 : pk, i, l, pi, F, Tq);
+    dem_particle<R, G, Off>(D, FUSE && odd ? pk2 : pk, i, l, T, pi, F, Tq);
     if (!own || (G > 1 && l != 0)) return;
     if constexpr (FUSE) {
         integrate_particle<R, true>(D, C, i, sub, F, Tq, pi, odd ? pk2 : pk, odd ? pk : pk2);
@@ -1977,6 +2029,8 @@ __global__ __launch_bounds__(kBlock, sizeof(R) == 4 && G == 1 ? 4 : 1) void k_de
 template <typename R>
 __global__ __launch_bounds__(kBlock) void k_dem_subcycle(Desc D, Cells<R> C, int sub_last)
 {
+    __shared__ __align__(16) char lds[kBlock / 64][kDemLds];
+    char *T = lds[threadIdx.x >> 6];
     const Parts &P = D.pt;
     const bool own = threadIdx.x < P.np;
     const int64_t i = own ? threadIdx.x : P.np - 1;
@@ -1986,7 +2040,7 @@ __global__ __launch_bounds__(kBlock) void k_dem_subcycle(Desc D, Cells<R> C, int
         if (wave) {
             double F[3], Tq[3];
             PV pi;
-            dem_particle<R, 1, uint32_t>(D, a, i, 0, pi, F, Tq);
+            dem_particle<R, 1, uint32_t>(D, a, i, 0, T, pi, F, Tq);
             if (own) integrate_particle<R, true>(D, C, i, t == D.p.n_dem - 1 ? sub_last : 0, F, Tq, pi, a, b);
         }
         __syncthreads();
@@ -2877,22 +2931,22 @@ static inline int dem_lanes(const Desc &D)
     if (n > 131072 || mean < 6.0) return 1;
     return n <= 32768 && mean >= 12.0 ? 8 : 2;
 }
-template <typename R, bool FUSE>
+template <typename R, bool FUSE, bool LISTS>
 static void launch_dem(const Desc &D, const Cells<R> &C, int sub, int odd, hipStream_t s)
 {
     if (D.pt.np == 0) return;
     const int g = dem_lanes(D);
     const dim3 grid(nblocks(D.pt.np * g)), blk(kBlock);
-    if (g == 8) hipLaunchKernelGGL((k_dem_force<R, 8, FUSE, uint32_t>), grid, blk, 0, s, D, C, sub, odd);
-    else if (g == 2) hipLaunchKernelGGL((k_dem_force<R, 2, FUSE, uint32_t>), grid, blk, 0, s, D, C, sub, odd);
+    if (g == 8) hipLaunchKernelGGL((k_dem_force<R, 8, FUSE, uint32_t, LISTS>), grid, blk, 0, s, D, C, sub, odd);
+    else if (g == 2) hipLaunchKernelGGL((k_dem_force<R, 2, FUSE, uint32_t, LISTS>), grid, blk, 0, s, D, C, sub, odd);
     else if ((uint64_t)D.pt.np * sizeof(DemRec<R>) <= UINT32_MAX)
-        hipLaunchKernelGGL((k_dem_force<R, 1, FUSE, uint32_t>), grid, blk, 0, s, D, C, sub, odd);
+        hipLaunchKernelGGL((k_dem_force<R, 1, FUSE, uint32_t, LISTS>), grid, blk, 0, s, D, C, sub, odd);
     else
-        hipLaunchKernelGGL((k_dem_force<R, 1, FUSE, uint64_t>), grid, blk, 0, s, D, C, sub, odd);
+        hipLaunchKernelGGL((k_dem_force<R, 1, FUSE, uint64_t, LISTS>), grid, blk, 0, s, D, C, sub, odd);
 }
 template <typename R> void launch_dem_force(const Desc &D, const Cells<R> &C, hipStream_t s)
 {
-    launch_dem<R, false>(D, C, 0, 0, s);
+    launch_dem<R, false, false>(D, C, 0, 0, s);
 }
 bool dem_substep_fused(const Desc &D)
 {
@@ -2908,16 +2962,31 @@ bool dem_subcycle_single(const Desc &D)
 {
     return dem_substep_fused(D) && D.p.n_dem > 1 && D.pt.np <= kBlock && dem_lanes(D) == 1;
 }
-template <typename R>
-void launch_dem_substep_fused(const Desc &D, const Cells<R> &C, int sub, int last, int step_end, hipStream_t s)
+// Whether the fused pass builds the lists itself: with one DEM substep, whose launch
+// is all that a subcycle has (in passes with more of them the code costs more than
+// the launch of 4 us that it saves: single-launch subcycles of impact
+// 1.49 -> 1.56 ms with it). The pass's two request flags alternate from subcycle to
+// subcycle, and must from step to step.
+bool dem_builds_lists(const Desc &D)
 {
-    if (dem_subcycle_single(D)) {
-        if (D.pt.np > 0)
-            hipLaunchKernelGGL(k_dem_subcycle<R>, dim3(1), dim3((unsigned)((D.pt.np + 63) / 64 * 64)), 0, s, D, C,
-                               sub_flags(D, 1, step_end));
-        return;
-    }
-    launch_dem<R, true>(D, C, sub_flags(D, last, step_end), sub & 1, s);
+    return dem_substep_fused(D) && D.p.n_int % 2 == 0 && D.p.n_dem == 1;
+}
+int dem_served_requests(const Desc &D, int k)
+{
+    return (k == 0 ? 2 : 0) | (dem_builds_lists(D) && k % 2 == 0 ? 4 : 1);
+}
+template <typename R>
+void launch_dem_substep_fused(const Desc &D, const Cells<R> &C, int k, int sub, hipStream_t s)
+{
+    if (D.pt.np == 0) return;
+    const bool single = dem_subcycle_single(D);
+    const int f = sub_flags(D, single || sub == D.p.n_dem - 1, k == D.p.n_int - 1);
+    if (dem_builds_lists(D))
+        launch_dem<R, true, true>(D, C, f | (k % 2 ? SUB_REQ2 : SUB_REQ0), 0, s);
+    else if (single)
+        hipLaunchKernelGGL(k_dem_subcycle<R>, dim3(1), dim3((unsigned)((D.pt.np + 63) / 64 * 64)), 0, s, D, C, f);
+    else
+        launch_dem<R, true, false>(D, C, f, sub & 1, s);
 }
 bool dem_sorts_lengths(const Desc &D) { return sort_lengths(D); }
 // slots into the order of the sorted list, or the blocked one, if due
@@ -2933,13 +3002,13 @@ void launch_reorder(const Desc &D, hipStream_t s)
     hipLaunchKernelGGL(k_reorder, dim3(nblocks(D.pt.np)), dim3(kBlock), 0, s, D);
     hipLaunchKernelGGL(k_reorder_back, dim3(nblocks(D.pt.np, kBlock)), dim3(kBlock), 0, s, D);
 }
-void launch_nlist(const Desc &D, int first, hipStream_t s)
+template <typename R> void launch_nlist(const Desc &D, hipStream_t s)
 {
     if (D.pt.np <= 0) return;
     // few workgroups, as most launches find nothing to do (one wavefront per
     // particle at a build)
     const int64_t nb = (D.pt.np + kBlock / 64 - 1) / (kBlock / 64);
-    hipLaunchKernelGGL(k_nlist, dim3((unsigned)(nb < 2048 ? nb : 2048)), dim3(kBlock), 0, s, D, first);
+    hipLaunchKernelGGL(k_nlist<R>, dim3((unsigned)(nb < 2048 ? nb : 2048)), dim3(kBlock), 0, s, D);
 }
 template <typename R> void launch_integrate(const Desc &D, const Cells<R> &C, int last, int step_end, hipStream_t s)
 {
@@ -2988,7 +3057,8 @@ void launch_set_step(long long *stepc, long long v, hipStream_t s)
     template void launch_cellfields<R>(const Desc &, const Cells<R> &, hipStream_t);                       \
     template void launch_curl<R>(const Desc &, const Cells<R> &, hipStream_t);                            \
     template void launch_dem_force<R>(const Desc &, const Cells<R> &, hipStream_t);                       \
-    template void launch_dem_substep_fused<R>(const Desc &, const Cells<R> &, int, int, int, hipStream_t); \
+    template void launch_dem_substep_fused<R>(const Desc &, const Cells<R> &, int, int, hipStream_t);      \
+    template void launch_nlist<R>(const Desc &, hipStream_t);                                              \
     template void launch_integrate<R>(const Desc &, const Cells<R> &, int, int, hipStream_t);              \
     template void launch_part_am<R>(const Desc &, const Cells<R> &, hipStream_t);                          \
     template void launch_gather_am<R>(const Desc &, const Cells<R> &, hipStream_t);                        \

@@ -149,3 +149,30 @@ def test_few_particles_match_oracle(L, k, precision, tol):
         errs, bad = compare_states(dom.lbdem_get_state(), o.state, p, tol)
     print(f"{k} {precision}: {errs}", flush=True)
     assert not bad, errs
+
+
+@pytest.mark.parametrize("n_int", [2, 3, 10])
+@pytest.mark.parametrize("eps,h_c", [(0.05, 0.5), (0.1, 0.5), (0.1, 1.0)])
+@pytest.mark.parametrize("precision", ["fp64", "fp32dev"])
+def test_lists_built_in_substep_bitwise_equal(L, n_int, eps, h_c, precision):
+    """Neighbour lists rebuilt inside the fused pass of one DEM substep (even
+    n_int; one, two and eight lanes per particle) and by their own launch:
+    heavy spheres that drift by four times the distance of a rebuild."""
+    p = I.Params(n=(12, 13, 14), periodic=(1, 1, 1), tau=0.8, h_c=h_c, n_int=n_int, n_dem=1, precision=precision)
+    parts = I.make_particles(7, p, I.count_for_fraction(eps, 12 * 13 * 14, 0.5), 0.5, 0.5, 200.0)
+    parts.u[:] = (0.03, 0.02, -0.01)
+    print(f"{precision} {n_int} {h_c}: {parts.n} spheres", flush=True)
+    ref = None
+    for fuse in (1, 0):
+        with L.Domain(p) as dom:
+            dom.add(parts)
+            dom.lbdem_set_tuning(fuse_substep=fuse)
+            for _ in range(4):
+                dom.step(2)
+            st = dom.lbdem_get_state()
+        if ref is None:
+            ref = st
+            moved = np.linalg.norm((st["x"] - parts.x + 0.5 * np.array(p.n)) % p.n - 0.5 * np.array(p.n), axis=1)
+            assert moved.min() > 4 * 0.05
+        for key in ("df", "x", "u", "w", "a"):
+            assert np.array_equal(ref[key], st[key]), key
