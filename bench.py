@@ -196,6 +196,34 @@ def kernel_bytes(case, nlist, dem_order=0, fused=False):
             "curl": nc * 6 * rs}
 
 
+def launch_bytes(case, nlist, dem_order, fused):
+    """kernel_bytes with the classes that slots fixed between list rebuilds and
+    the records of both storage forms make cheaper:
+
+      nlist           nothing but the request is read where no rebuild is due    0
+      dem_force       with the integration: per particle list length, record,
+      (fused)         u, F_const, x_start read, u and the new record written,
+                      L slots read; in the FP32 form also rho
+                                100 B [+ 8] + 2 records (64 or 96 B) + 4 L B
+                      a lone substep also leaves x, a, the stencil and F_am and
+                      reads the build position instead of x_start, per cell
+                      Du/Dt                            84 B + 9 ws and 4 rs more
+      bins            per particle position's cell, list entry (12 B) and its
+                      order by id (12 B); per cell count, scan, offsets (20 B)
+    """
+    kb = kernel_bytes(case, nlist, dem_order, fused)
+    n = int(case.particles.n)
+    fp32 = case.params.precision == "fp32dev"
+    kb["nlist"] = 0
+    kb["bins"] = n * 24 + int(np.prod(case.params.n)) * 20
+    if fused:
+        rs = ws = 4 if fp32 else 8
+        kb["dem_force"] = int(n * ((236 if fp32 else 292) + 4 * nlist))
+        if case.params.n_dem == 1:
+            kb["dem_force"] += n * (84 + 9 * ws) + int(np.prod(case.params.n)) * 4 * rs
+    return kb
+
+
 # DEM pair arithmetic (a8): about 150 FP64 flops per pair evaluation within
 # the interaction reach (2 square roots, a logarithm and 2-3 divisions among
 # them); each unordered pair is evaluated from both of its particles.
@@ -542,9 +570,9 @@ def run_step_workload(lbdem, torch, case, wl_name, K, W, ksteps, stream, args):
     nreach = mean_list_length(case, vskin=0.0)
     print(f"[bench] mean Verlet-list length {nlist:.2f}, neighbours within reach {nreach:.2f}",
           file=sys.stderr, flush=True)
-    dem_order = tuning["dem_order"] if tuning["dem_order"] >= 0 else int(case.particles.n >= 1 << 20)
-    fused = (tuning.get("fuse_substep", -1) == 1 and case.params.precision == "fp32dev" and case.params.n_dem >= 3)
-    kb = kernel_bytes(case, nlist, dem_order, fused)
+    dem_order = tuning["dem_order"] if tuning["dem_order"] >= 0 else int(case.particles.n >= 1 << 18)
+    fused = tuning.get("fuse_substep", -1) != 0
+    kb = launch_bytes(case, nlist, dem_order, fused)
     npairs = nreach * case.particles.n
     roofs = {k: roofline_entry(k, times, kb, wl_name, variant, npairs) for k in times
              if times[k]["launches_per_step"] > 0}

@@ -1767,7 +1767,7 @@ __device__ __forceinline__ void integrate_particle(const Desc &D, const Cells<R>
 // FP64 instruction issue (71 % of the SIMD cycles without the integration, 58 %
 // with it) and by the latency of the record gathers. Forces and integration of a
 // substep of 3.17 M dense spheres (29.6 list entries each): 1.28 ms as two
-// passes with a lane per record, 0.84 ms. Not kept: non-temporal loads of the
+// passes with a lane per record, 0.78 ms. Not kept: non-temporal loads of the
 // lists or of the state touched once (0 to +7 % time).
 // The minimum image is skipped by wavefronts with no particle within reach of a
 // periodic boundary.
@@ -2045,7 +2045,7 @@ __global__ __launch_bounds__(kBlock, sizeof(R) == 4 && G == 1 ? 4 : 1) void k_de
 // All substeps of a subcycle in one launch of one workgroup, for particles that
 // fit into one (np <= kBlock, one lane each, short lists): a substep of so few
 // takes less time than its launch. The particles meet at a barrier after every substep; the
-// records alternate as above. One sphere at a wall, 50 substeps: 117 us,
+// records alternate as above. One sphere at a wall, 50 substeps: 97 us,
 // 280 us as 50 launches (and twice that as 100 with the integration apart).
 template <typename R>
 __global__ __launch_bounds__(kBlock) void k_dem_subcycle(Desc D, Cells<R> C, int sub_last)
