@@ -303,13 +303,14 @@ void resolve_phys(lbdem_domain_t h)
     P.kn_per_m = (M_PI * M_PI + L * L) / (P.T_c * P.T_c);
     P.xi_per_m = -2.0 * L / P.T_c;
     P.c_am = p.c_am;
-    // a particle may move at most `skin` within one subcycle (else the step
-    // is flagged unstable); Verlet lists carry `vskin` beyond the interaction
-    // reach and are rebuilt once a particle has moved vskin/2 - skin since
-    // the build, so every pair within reach stays listed. A fifth of a
-    // tenth of a cell per subcycle is far above the settling speeds of these
-    // workloads (1e-4 cells per step at most), and a thin skin keeps the
-    // lists close to the pairs within reach.
+    // a particle may move at most `skin` per axis within one subcycle (else the
+    // step is flagged unstable); Verlet lists carry `vskin` beyond the
+    // interaction reach and are rebuilt ahead of a subcycle in which a particle
+    // could get vskin/2 away from where it was at the build, so every pair
+    // within reach stays listed (vskin/2 must exceed sqrt(3) skin for lists to
+    // outlive a subcycle). A fifth of a tenth of a cell per subcycle is far
+    // above the settling speeds of these workloads (1e-4 cells per step at
+    // most), and a thin skin keeps the lists close to the pairs within reach.
     P.skin = 0.02;
     P.vskin = 0.1;
     P.rbin = 1;

@@ -1464,8 +1464,8 @@ __device__ __forceinline__ void min_image(const Geo &g, double dx[3])
 // (d_i + d_j)/2 + h_c). A list holds the slots of every particle within that
 // reach plus a skin, in ascending insertion index, so the force sums run in an
 // order that does not depend on when the list was built. Rebuilt only when a
-// particle has moved more than (skin/2 - per-subcycle limit) since the build;
-// slots do not move between two builds.
+// particle could move half the skin from where it was at the build within the
+// next subcycle (integrate_particle); slots do not move between two builds.
 //
 // One wavefront per particle: the lanes take the rows of bins around it, then
 // the candidates of those rows (found by a search in the rows' running counts);
@@ -1690,7 +1690,7 @@ __device__ __forceinline__ void integrate_particle(const Desc &D, const Cells<R>
     const bool spin = !FUSED || __any(Tq[0] != 0.0 || Tq[1] != 0.0 || Tq[2] != 0.0);
     if (!spin) load_spin<R>(src, i, w);
     int bad = 0;
-    double moved = 0.0;
+    double ahead2 = 0.0;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         const int64_t k = a * cap + i;
@@ -1723,20 +1723,25 @@ __device__ __forceinline__ void integrate_particle(const Desc &D, const Cells<R>
             P.a[k] = acc[a];
             double db = xa - xb[a];
             if (D.g.per[a]) db -= L * rint(db / L);
-            moved = fmax(moved, fabs(db));
+            const double reach = fabs(db) + D.p.skin;
+            ahead2 += reach * reach;
         }
     }
     if (bad) atomicOr(D.flags, bad);
     // the record feeds the next substep's pair loop
     store_rec<R>(rec, i, x, u, w, d, FUSED ? (R)own.m : (R)m);
     if (!(sub & SUB_LAST)) return;
-    // with at most `skin` per subcycle, rebuilding once any particle has moved
-    // vskin/2 - skin keeps every pair within the list reach until the rebuild.
-    // At a step's end the reordering (and with it the rebuild) is asked for a
-    // little earlier, so that rebuilds fall on step starts, after a reordering.
-    const double limit = 0.5 * D.p.vskin - D.p.skin;
-    if (moved > limit) P.need[sub & SUB_REQ0 ? 2 : 0] = P.need[1] = 1;
-    else if ((sub & SUB_END) && moved > 0.8 * limit) P.need[1] = 1;
+    // A list holds every pair within reach as long as no particle has moved
+    // vskin/2 since its build. The next subcycle adds at most `skin` per axis
+    // (else it is flagged), so the farthest a particle can get in it is the
+    // corner |db| + skin of a box: rebuild first where that lies vskin/2 away.
+    // (Comparing the axes one by one with vskin/2 - skin would let two spheres
+    // close in by 0.17 along a diagonal, with a skin of 0.1.) At a step's end the
+    // reordering (and with it the rebuild) is asked for a little earlier, so that
+    // rebuilds fall on step starts, after a reordering.
+    const double limit2 = 0.25 * D.p.vskin * D.p.vskin;
+    if (ahead2 > limit2) P.need[sub & SUB_REQ0 ? 2 : 0] = P.need[1] = 1;
+    else if ((sub & SUB_END) && ahead2 > 0.92 * 0.92 * limit2) P.need[1] = 1;
     atomicAdd(&D.b.cnt[particle_cell(D.g, x[0], x[1], x[2])], 1);
     // the stencil of a position outside the domain or not finite is not taken
     // (the step is flagged, the state no longer meaningful)
