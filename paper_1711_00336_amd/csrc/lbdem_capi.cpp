@@ -403,8 +403,11 @@ void rebuild_particle_fields(lbdem_domain_t h)
     launch_bin_count(h->desc(), h->stream);
     launch_bin_build(h->desc(), h->stream);
     launch_reorder(h->desc(), h->stream);
-    if (dem_sorts_lengths(h->desc())) {  // once more with the lengths known
-        launch_nlist<R>(h->desc(), h->stream);
+    // once more with the lengths known. Lists that overflow here need not do so
+    // in the first step, which builds its own: particles may yet be added, and
+    // the capacity goes by their number
+    if (dem_sorts_lengths(h->desc())) {
+        launch_nlist<R>(h->desc(), h->stream, false);
         launch_reorder(h->desc(), h->stream);
     }
     launch_set_int(h->pt.need + 1, 0, h->stream);

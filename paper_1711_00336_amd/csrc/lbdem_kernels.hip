@@ -1516,9 +1516,11 @@ __device__ __forceinline__ void load_sphere(const DemRec<R> *pk, int64_t i, doub
 
 // the list of slot i, by one wavefront; lds: 2 kListLds ints of its own. Positions
 // come from the records pk of the subcycle's start: the state arrays may already
-// hold another workgroup's new ones.
+// hold another workgroup's new ones. Neighbours beyond the capacity raise
+// FLAG_NLIST if `judge`.
 template <typename R>
-__device__ __forceinline__ void build_list(const Desc &D, const DemRec<R> *pk, int64_t i, int lane, int *lds)
+__device__ __forceinline__ void build_list(const Desc &D, const DemRec<R> *pk, int64_t i, int lane, int *lds,
+                                           bool judge)
 {
     const Parts &P = D.pt;
     int *sid = lds, *ssl = lds + kListLds;
@@ -1591,7 +1593,7 @@ __device__ __forceinline__ void build_list(const Desc &D, const DemRec<R> *pk, i
         }
     }
     if (m > P.nbr) {
-        if (lane == 0) atomicOr(D.flags, FLAG_NLIST);
+        if (judge && lane == 0) atomicOr(D.flags, FLAG_NLIST);
         m = P.nbr;
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -1624,7 +1626,7 @@ __device__ __forceinline__ void build_list(const Desc &D, const DemRec<R> *pk, i
     }
 }
 
-template <typename R> __global__ __launch_bounds__(kBlock) void k_nlist(Desc D)
+template <typename R> __global__ __launch_bounds__(kBlock) void k_nlist(Desc D, bool judge)
 {
     __shared__ int lds[kBlock / 64][2 * kListLds];
     const Parts &P = D.pt;
@@ -1633,7 +1635,8 @@ template <typename R> __global__ __launch_bounds__(kBlock) void k_nlist(Desc D)
     // a workgroup takes a run of slots, whose candidates it then finds in its cache
     const int64_t per = (P.np + gridDim.x - 1) / gridDim.x, b0 = xcd_remap(blockIdx.x, gridDim.x) * per;
     const int64_t b1 = b0 + per < P.np ? b0 + per : P.np;
-    for (int64_t i = b0 + wv; i < b1; i += kBlock / 64) build_list<R>(D, (const DemRec<R> *)P.pk, i, lane, lds[wv]);
+    for (int64_t i = b0 + wv; i < b1; i += kBlock / 64)
+        build_list<R>(D, (const DemRec<R> *)P.pk, i, lane, lds[wv], judge);
 }
 
 // what the last substep of a subcycle does besides integrating
@@ -2008,7 +2011,7 @@ __device__ __forceinline__ void dem_lists(const Desc &D, int sub, const DemRec<R
     if (D.pt.need[sub & SUB_REQ2 ? 2 : 0] == 0) return;
     if (!halted(D))
         for (int k = threadIdx.x >> 6; k < n && i0 + k < D.pt.np; k += blockDim.x >> 6)
-            build_list<R>(D, pk, i0 + k, threadIdx.x & 63, (int *)lds);
+            build_list<R>(D, pk, i0 + k, threadIdx.x & 63, (int *)lds, true);
     __syncthreads();
 }
 
@@ -3028,13 +3031,13 @@ void launch_reorder(const Desc &D, hipStream_t s)
     hipLaunchKernelGGL(k_reorder, dim3(nblocks(D.pt.np)), dim3(kBlock), 0, s, D);
     hipLaunchKernelGGL(k_reorder_back, dim3(nblocks(D.pt.np, kBlock)), dim3(kBlock), 0, s, D);
 }
-template <typename R> void launch_nlist(const Desc &D, hipStream_t s)
+template <typename R> void launch_nlist(const Desc &D, hipStream_t s, bool judge)
 {
     if (D.pt.np <= 0) return;
     // few workgroups, as most launches find nothing to do (one wavefront per
     // particle at a build)
     const int64_t nb = (D.pt.np + kBlock / 64 - 1) / (kBlock / 64);
-    hipLaunchKernelGGL(k_nlist<R>, dim3((unsigned)(nb < 2048 ? nb : 2048)), dim3(kBlock), 0, s, D);
+    hipLaunchKernelGGL(k_nlist<R>, dim3((unsigned)(nb < 2048 ? nb : 2048)), dim3(kBlock), 0, s, D, judge);
 }
 template <typename R> void launch_integrate(const Desc &D, const Cells<R> &C, int last, int step_end, hipStream_t s)
 {
@@ -3084,7 +3087,7 @@ void launch_set_step(long long *stepc, long long v, hipStream_t s)
     template void launch_curl<R>(const Desc &, const Cells<R> &, hipStream_t);                            \
     template void launch_dem_force<R>(const Desc &, const Cells<R> &, hipStream_t);                       \
     template void launch_dem_substep_fused<R>(const Desc &, const Cells<R> &, int, int, hipStream_t);      \
-    template void launch_nlist<R>(const Desc &, hipStream_t);                                              \
+    template void launch_nlist<R>(const Desc &, hipStream_t, bool);                                        \
     template void launch_integrate<R>(const Desc &, const Cells<R> &, int, int, hipStream_t);              \
     template void launch_part_am<R>(const Desc &, const Cells<R> &, hipStream_t);                          \
     template void launch_gather_am<R>(const Desc &, const Cells<R> &, hipStream_t);                        \

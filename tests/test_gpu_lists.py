@@ -46,3 +46,44 @@ def test_diagonal_approach_matches_oracle(L, n_dem, use_lub, shift):
         errs, bad = compare_states(dom.lbdem_get_state(), o.state, p, 1e-12)
     print(f"n_dem {n_dem} lubrication {use_lub} at {x[0]}: {errs}", flush=True)
     assert not bad, errs
+
+
+def _cluster_and_rest(d):
+    """A cluster whose spheres have more neighbours than the lists of a domain
+    with the cluster alone hold (56 against 32), and a filling with which they
+    hold 64."""
+    g = np.stack(np.meshgrid(*[np.arange(5)] * 3, indexing="ij"), -1).reshape(-1, 3)
+    cluster = 4.0 + 0.49 * (g - 2)
+    g = np.stack(np.meshgrid(*[np.arange(11)] * 3, indexing="ij"), -1).reshape(-1, 3)
+    rest = (g + 0.5) * 8.0 / 11.0
+    rest = rest[np.linalg.norm(rest[:, None] - cluster[None], axis=-1).min(1) > 0.6]
+
+    def parts(x):
+        k = len(x)
+        return I.Particles(x, np.zeros((k, 3)), np.zeros((k, 3)), np.full(k, d), np.full(k, 2.5))
+    return parts(cluster), parts(rest), parts(np.concatenate([cluster, rest]))
+
+
+@pytest.mark.parametrize("n_dem", [1, 3])
+def test_crowded_spheres_may_be_added_first(L, n_dem):
+    """Adding particles judges no list: lists that would overflow with the
+    first addition, and not with the second, are built by the first step."""
+    from tests.parity_util import compare_states
+    from oracle import oracle as O
+    p = I.Params(n=(8, 8, 8), periodic=(1, 1, 1), tau=I.SWEEP_TAU, h_c=0.6, n_int=10, n_dem=n_dem)
+    cluster, rest, both = _cluster_and_rest(0.48)
+    o = O.Oracle(p, both)
+    assert o.step(1)["status"] == 0
+    with L.Domain(p) as dom:
+        dom.add(cluster)
+        dom.lbdem_sync()
+        dom.add(rest)
+        dom.step(1)
+        errs, bad = compare_states(dom.lbdem_get_state(), o.state, p, 1e-12)
+    print(f"n_dem {n_dem}: {errs}", flush=True)
+    assert not bad, errs
+    with L.Domain(p) as dom:  # a step on the cluster alone is flagged, as ever
+        dom.add(cluster)
+        with pytest.raises(L.LbdemError) as e:
+            dom.step(1)
+        assert e.value.status == L.E_UNSTABLE
