@@ -217,10 +217,13 @@ lbdem_status lbdem_step(lbdem_domain_t h, int64_t nsteps);
 lbdem_status lbdem_sync(lbdem_domain_t h);
 
 /* Copy one field (FP64, [ncomp][Nc]) to host or device memory `out`
- * (caller-owned, ncomp*Nc doubles). Synchronous. */
+ * (caller-owned, ncomp*Nc doubles). Synchronous. Runs on the domain's stream:
+ * work pending on other streams that writes `out` must be complete. */
 lbdem_status lbdem_read_field(lbdem_domain_t h, int field, int mem_kind, double *out);
 
-/* Particle data in insertion order: x, u, omega, accel [np][3] (NULL skips). */
+/* Particle data in insertion order: x, u, omega, accel [np][3] (NULL skips), to
+ * host or device memory. Synchronous, after the domain's stream and after work
+ * pending on the default stream. */
 lbdem_status lbdem_read_particles(lbdem_domain_t h, int mem_kind, double *x, double *u,
                                   double *omega, double *accel);
 

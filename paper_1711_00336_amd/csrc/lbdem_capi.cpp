@@ -517,6 +517,9 @@ struct HostParticles {
 // into the permutation targets, then each array is one copy. Four vectors of
 // 3.17 M spheres to the host: 31 ms (9.9 GB/s, the copy to pageable memory),
 // 205 ms when the host transposed and scattered every vector itself.
+// Work that the caller has pending on the default stream may still write the
+// destination (a fill, a copy to pinned memory): the copies wait for it, as a
+// copy on that stream would.
 void read_particle_state(lbdem_domain_t h, hipMemcpyKind kind, double *x, double *u, double *w, double *a, double *d,
                          double *rho)
 {
@@ -529,6 +532,7 @@ void read_particle_state(lbdem_domain_t h, hipMemcpyKind kind, double *x, double
     if (n == 0 || what == 0) return;
     launch_pack_particles(h->desc(), what, h->stream);
     hip_check(hipGetLastError(), "particle read-out");
+    hip_check(hipStreamSynchronize(nullptr), "sync");
     for (int t = 0; t < 6; ++t)
         if (dst[t])
             hip_check(hipMemcpyAsync(dst[t], src[t], sizeof(double) * (size_t)(t < 4 ? 3 * n : n), kind, h->stream),

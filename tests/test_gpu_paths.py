@@ -176,3 +176,33 @@ def test_lists_built_in_substep_bitwise_equal(L, n_int, eps, h_c, precision):
             assert moved.min() > 4 * 0.05
         for key in ("df", "x", "u", "w", "a"):
             assert np.array_equal(ref[key], st[key]), key
+
+
+def test_read_out_follows_pending_default_stream_work(L):
+    """A read-out into memory that work pending on the default stream still
+    writes: the read-out comes last, to device and to pinned host memory."""
+    import torch
+    p = I.Params(n=(21, 17, 30), periodic=(1, 1, 0), tau=0.8, precision="fp64")
+    n = 300
+    parts = I.make_particles(2, p, n, 0.5, 0.5, 2.5)
+    call = L.lib().lbdem_read_particles
+    with L.Domain(p) as dom:
+        dom.add(parts)
+        dom.step(2)
+        want = dom.lbdem_read_particles()
+        dev = [torch.empty(n, 3, dtype=torch.float64, device="cuda") for _ in range(4)]
+        pin = [torch.empty(n, 3, dtype=torch.float64, pin_memory=True) for _ in range(4)]
+        seven = torch.full((n, 3), 7.0, dtype=torch.float64, device="cuda")
+        a = torch.randn(8192, 8192, device="cuda")
+        b = a @ a
+        for mem, out in ((L.MEM_DEVICE, dev), (L.MEM_HOST, pin)):
+            torch.cuda.synchronize()
+            for _ in range(20):  # a tenth of a second and more
+                torch.matmul(a, a, out=b)
+            for t in out:
+                t.copy_(seven, non_blocking=True)
+            assert call(dom.h, mem, *[C.c_void_p(t.data_ptr()) for t in out]) == L.OK
+            torch.cuda.synchronize()
+            for w, t in zip(want, out):
+                same = np.array_equal(w, t.cpu().numpy())
+                assert same, mem
