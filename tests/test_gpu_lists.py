@@ -87,3 +87,91 @@ def test_crowded_spheres_may_be_added_first(L, n_dem):
         with pytest.raises(L.LbdemError) as e:
             dom.step(1)
         assert e.value.status == L.E_UNSTABLE
+
+
+def _list_builds(u, n_int, steps):
+    """(step, subcycle) of every list build for spheres in straight flight at u:
+    the rebuild rule on the host."""
+    skin, c = 0.02, 0.05
+    need = early = True
+    builds, moved = [], np.zeros_like(u)
+    for s in range(steps):
+        need, early = need or early, False
+        for k in range(n_int):
+            if need:
+                builds.append((s, k))
+                moved[:] = 0.0
+                need = False
+            moved += u / n_int
+            ahead = np.sqrt(((np.abs(moved) + skin) ** 2).sum(1)).max()
+            if ahead > c:
+                need = early = True
+            elif k == n_int - 1 and ahead > 0.92 * c:
+                early = True
+    return builds
+
+
+@pytest.mark.parametrize("n_int,speed", [(10, 0.037), (2, 0.0062)])
+@pytest.mark.parametrize("eps,h_c", [(0.05, 0.5), (0.1, 0.5), (0.1, 1.0)])
+@pytest.mark.parametrize("precision", ["fp64", "fp32dev"])
+def test_lists_built_at_odd_subcycles(L, n_int, speed, eps, h_c, precision):
+    """Lists built inside the pass of one DEM substep, at odd and at even
+    subcycles in mid-step: heavy spheres with soft contacts in nearly straight
+    diagonal flight, half of them the other way, so that pairs come within
+    reach between the builds. One, two and eight lanes per particle. Against
+    the oracle (the bars of free-running steps) and, bit for bit, against
+    lists built by their own launch."""
+    from tests.parity_util import compare_states
+    from oracle import oracle as O
+    n, steps = (8, 9, 10), 3 if n_int == 10 else 4
+    p = I.Params(n=n, periodic=(1, 1, 1), tau=0.55, h_c=h_c, h_min=0.2, T_c=1e4, n_int=n_int, n_dem=1,
+                 precision=precision)
+    parts = I.make_particles(7, p, I.count_for_fraction(eps, 8 * 9 * 10, 0.5), 0.5, 0.5, 2000.0)
+    parts.u[::2] = speed
+    parts.u[1::2] = -speed
+    odd = [k for _, k in _list_builds(0.97 * parts.u, n_int, steps) if k % 2]
+    assert odd and any(k % 2 for _, k in _list_builds(parts.u, n_int, steps))
+    o = O.Oracle(p, parts)
+    assert o.step(steps)["status"] == 0
+    assert np.abs(o.state.u / parts.u - 1.0).max() < 0.03
+    ref = None
+    for fuse in (1, 0):
+        with L.Domain(p) as dom:
+            dom.add(parts)
+            dom.lbdem_set_tuning(fuse_substep=fuse)
+            dom.step(steps)
+            st = dom.lbdem_get_state()
+        if ref is None:
+            ref = st
+            errs, bad = compare_states(st, o.state, p, 1e-10 if precision == "fp64" else 1e-5 * steps)
+            print(f"{precision} {n_int}: {parts.n} spheres, odd builds {odd}, {errs}", flush=True)
+            assert not bad, errs
+        for key in ("df", "x", "u", "w", "a"):
+            assert np.array_equal(ref[key], st[key]), key
+
+
+@pytest.mark.parametrize("fuse", [1, 0])
+@pytest.mark.parametrize("inwards", [True, False])
+@pytest.mark.parametrize("precision", ["fp64", "fp32dev"])
+def test_request_of_an_even_subcycle_is_served(L, precision, inwards, fuse):
+    """That the second subcycle of a step builds lists which the first asked
+    for: forty spheres just outside the list reach of one fly into it during
+    the first, and its list (of 32 places) overflows at the second's build.
+    Flying outwards, none does."""
+    p = I.Params(n=(12, 12, 12), periodic=(1, 1, 1), tau=0.55, h_c=0.5, n_int=2, n_dem=1, precision=precision)
+    t = np.arange(40) + 0.5
+    z, phi = 1.0 - t / 20.0, np.pi * (1.0 + np.sqrt(5.0)) * t
+    e = np.stack([np.sqrt(1.0 - z * z) * np.cos(phi), np.sqrt(1.0 - z * z) * np.sin(phi), z], axis=1)
+    x = 6.0 + np.concatenate([np.zeros((1, 3)), 1.11 * e])
+    u = np.concatenate([np.zeros((1, 3)), (-0.039 if inwards else 0.039) * e])
+    assert [k for _, k in _list_builds(0.98 * u, 2, 1)] == [0, 1]
+    parts = I.Particles(x, u, np.zeros((41, 3)), np.full(41, 0.5), np.full(41, 2000.0))
+    with L.Domain(p) as dom:
+        dom.add(parts)
+        dom.lbdem_set_tuning(fuse_substep=fuse)
+        if inwards:
+            with pytest.raises(L.LbdemError, match="more neighbours") as err:
+                dom.step(1)
+            assert err.value.status == L.E_UNSTABLE
+        else:
+            dom.step(1)
