@@ -206,3 +206,111 @@ def test_read_out_follows_pending_default_stream_work(L):
             for w, t in zip(want, out):
                 same = np.array_equal(w, t.cpu().numpy())
                 assert same, mem
+
+
+@pytest.mark.parametrize("n,precision", [((83, 81, 79), "fp32dev"), ((61, 53, 71), "fp64"), ((61, 53, 11), "fp64"),
+                                         ((35, 33, 31), "fp32dev")])
+def test_ragged_drag_tiles_bitwise_equal(L, n, precision):
+    """Every drag tile where it does not divide the domain (FP32 16x8x8 from
+    2^19 cells on and 16x4x4 below, FP64 16x4x8 above 768 small tiles and
+    16x4x4 below), halos wrapped on two axes and clamped at the walls of the
+    third, against the pass with one thread per particle (variant 3)."""
+    p = I.Params(n=n, periodic=(1, 0, 1), tau=0.8, n_int=2, precision=precision)
+    rng = np.random.default_rng(n[0])
+    k = 3000
+    x = rng.random((k, 3)) * np.array(n)
+    x[:, 1] = np.clip(x[:, 1], 0.1, n[1] - 0.1)
+    x[:100, 0] = n[0] * (1.0 - 1e-9 * rng.random(100))  # last cells of each axis
+    x[100:200, 1] = n[1] - 0.1
+    x[200:300, 2] = n[2] * (1.0 - 1e-9 * rng.random(100))
+    parts = I.Particles(x, rng.normal(size=(k, 3)) * 1e-4, np.zeros((k, 3)), np.full(k, 0.2), np.full(k, 20.0))
+    df = I.perturbed_state(3, n[0] * n[1] * n[2], 1e-4)
+    ref = None
+    for v in (3, 0):
+        with L.Domain(p.copy(use_lub=0, T_c=1e3)) as dom:
+            dom.lbdem_set_state(df, np.zeros((3, dom.nc)), 0, parts.x, parts.u, parts.w, np.zeros((k, 3)), parts.d,
+                                parts.rho_p)
+            dom.lbdem_set_gather_variant(v)
+            dom.step(1)
+            st = dom.lbdem_read_particle_forces()
+            st["facc"] = dom.lbdem_read_field(L.FIELD_F_ACC)
+            st["x"], st["u"] = dom.lbdem_read_particles()[:2]
+        if ref is None:
+            ref = st
+            assert np.abs(st["F_d"]).max() > 0 and np.abs(st["F_pr"]).max() > 0
+        for key in ref:
+            same = np.array_equal(ref[key], st[key])
+            assert same, (v, key)
+
+
+@pytest.mark.parametrize("k", [192, 193, 255, 256, 257])
+@pytest.mark.parametrize("precision,tol", [("fp64", 1e-12), ("fp32dev", 1e-5)])
+def test_single_launch_subcycle_edges(L, k, precision, tol):
+    """The substeps of a subcycle in one launch of up to four full wavefronts,
+    its last particle count and the first beyond it, against the oracle after
+    one step and, bit for bit, against separate force and integration passes."""
+    from tests.parity_util import compare_states
+    from oracle import oracle as O
+    rng = np.random.default_rng(k)
+    p = I.Params(n=(16, 13, 14), periodic=(1, 0, 1), tau=0.8, h_c=0.5, n_int=10, n_dem=4, precision=precision)
+    d = np.full(k, 0.8)
+    x = I.place_spheres(k, p.n, p.periodic, d)
+    far = np.linalg.norm(x[:, None] - x[None], axis=-1) + 9.0 * np.eye(k)
+    pair = np.unravel_index(far.argmin(), far.shape)
+    d[list(pair)] = 1.01 * far.min()  # the closest pair overlaps by a hundredth
+    parts = I.Particles(x, rng.normal(size=(k, 3)) * 1e-4, rng.normal(size=(k, 3)) * 1e-4, d, np.full(k, 2.5))
+    o = O.Oracle(p, parts)
+    assert o.step(1)["status"] == 0
+    ref = None
+    for fuse in (1, 0):
+        with L.Domain(p) as dom:
+            dom.add(parts)
+            dom.lbdem_set_tuning(fuse_substep=fuse)
+            dom.step(1)
+            st = dom.lbdem_get_state()
+        if ref is None:
+            ref = st
+            errs, bad = compare_states(st, o.state, p, tol)
+            print(f"{k} {precision}: {errs}", flush=True)
+            assert not bad, errs
+        for key in ("df", "x", "u", "w", "a"):
+            assert np.array_equal(ref[key], st[key]), key
+
+
+@pytest.mark.parametrize("precision,t,tol", [("fp64", 9, 1e-10), ("fp32dev", 11, 1e-5)])
+def test_records_beyond_4_gib(L, precision, t, tol):
+    """Records that a 32-bit byte offset does not reach (46.7 M spheres of 96 B,
+    85 M of 64 B): a periodic box of t^3 copies of a small one steps as the
+    small one does. Positions 144 cells out carry 16 times its rounding (3e-14),
+    which the gaps (0.05 and more) turn into 1e-12 of a force: 1e-10 of the
+    largest velocity; in the FP32 form the rounding of single weights may turn
+    over: the bar of its steps."""
+    n, m = 16, 40  # 64,000 spheres on a jittered lattice, 15.6 per cell
+    rng = np.random.default_rng(4)
+    g = np.stack(np.meshgrid(*[np.arange(m)] * 3, indexing="ij"), -1).reshape(-1, 3)
+    x = (g + 0.5 + 0.06 * rng.uniform(-1, 1, g.shape)) * (n / m)
+    x = np.round(x * 2.0 ** 30) * 2.0 ** -30  # exact in every copy
+    k = len(x)
+    u = rng.normal(size=(k, 3)) * 1e-4
+    small = I.Params(n=(n,) * 3, periodic=(1, 1, 1), tau=I.SWEEP_TAU, h_c=0.1, n_int=2, n_dem=1,
+                     precision=precision)
+    with L.Domain(small) as dom:
+        dom.lbdem_add_particles(x, u, np.zeros((k, 3)), np.full(k, 0.3), np.full(k, 20.0))
+        dom.step(1)
+        want = dom.lbdem_read_particles()[1]
+    assert np.abs(want - u).max() > 1e-2 * np.abs(u).max()
+    off = np.stack(np.meshgrid(*[np.arange(t) * float(n)] * 3, indexing="ij"), -1).reshape(-1, 1, 3)
+    big = small.copy(n=(n * t,) * 3)
+    K = k * t ** 3
+    with L.Domain(big) as dom:
+        print(f"{K} spheres, {(96 if precision == 'fp64' else 64) * K / 2 ** 30:.2f} GiB of records", flush=True)
+        dom.lbdem_add_particles((off + x).reshape(-1, 3), np.tile(u, (t ** 3, 1)), np.zeros((K, 3)), np.full(K, 0.3),
+                                np.full(K, 20.0))
+        print("added", flush=True)
+        dom.step(1)
+        print("stepped", flush=True)
+        got = np.zeros((K, 3))
+        assert L.lib().lbdem_read_particles(dom.h, L.MEM_HOST, None, C.c_void_p(got.ctypes.data), None, None) == L.OK
+    err = np.abs(got.reshape(t ** 3, k, 3) - want).max() / np.abs(want).max()
+    print(f"largest difference {err}", flush=True)
+    assert err < tol
