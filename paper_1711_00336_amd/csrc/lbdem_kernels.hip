@@ -843,9 +843,11 @@ __global__ __launch_bounds__(TX *TY *TZ) void k_gather_tile(Desc D, Cells<R> C)
     // all of them at once in all but crowded tiles. A cell takes its three
     // planes in ascending order whatever the runs, so the order of its sum
     // does not depend on them.
-    for (int h0 = 0, h1; h0 < HZ; h0 = h1) {
+    for (int h0 = K > 0 ? 0 : HZ, h1; h0 < HZ; h0 = h1) {  // (empty tiles have nothing to sum)
         const int base = hoff[h0 * HX * HY];
-        h1 = h0 + 1;
+        // (the usual tile fits whole: searching for its last plane, a chain of LDS
+        // reads, would take longer than the rest of an empty one)
+        h1 = K - base <= KMAX ? HZ : h0 + 1;
         while (h1 < HZ && hoff[(h1 + 1) * HX * HY] - base <= KMAX) ++h1;
         const int nk = hoff[h1 * HX * HY] - base;
         if (h0 > 0) __syncthreads();
