@@ -757,7 +757,7 @@ void read_field_impl(lbdem_domain_t h, int field, double *dev_out)
         hip_check(hipGetLastError(), "read_field");
         return;
     case LBDEM_FIELD_J: vec4 = (const R *)h->j; break;
-    case LBDEM_FIELD_F_ACC: vec4 = (const R *)h->facc; break;
+    case LBDEM_FIELD_F_ACC: src = (const R *)h->facc; ncomp = 3; break;
     case LBDEM_FIELD_DUDT: vec4 = (const R *)h->dudt; break;
     case LBDEM_FIELD_GRADP: vec4 = (const R *)h->gradp; break;
     case LBDEM_FIELD_CURL: vec4 = (const R *)h->curl; break;
@@ -882,8 +882,9 @@ lbdem_status lbdem_create(const lbdem_params *p, void *hip_stream, lbdem_domain_
         h->epsp = h->dalloc(rs * nc);
         for (void **q : {&h->j, &h->dudt, &h->gradp, &h->fam, &h->uf, &h->facc, &h->curl}) {
             if (q == &h->curl && !h->phys.use_lift) continue;
-            *q = h->dalloc(rs * 4 * nc);
-            hip_check(hipMemsetAsync(*q, 0, rs * 4 * nc, h->stream), "memset");
+            const size_t ncomp = q == &h->facc || (q == &h->uf && h->prec == LBDEM_FP64) ? 3 : 4;
+            *q = h->dalloc(rs * ncomp * nc);
+            hip_check(hipMemsetAsync(*q, 0, rs * ncomp * nc, h->stream), "memset");
         }
         h->cnt = (int *)h->dalloc(sizeof(int) * nc);
         h->start = (int *)h->dalloc(sizeof(int) * (nc + 1));

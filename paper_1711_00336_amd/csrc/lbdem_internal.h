@@ -37,22 +37,25 @@ struct Phys {
     int rbin;                   // DEM search radius in cells (list build)
 };
 
-// Cell fields, [ncomp][nc] or, where a pass reads the vector of one cell (or of a
-// neighbour) whole, [nc][4] with a scalar that is read beside it.
-// R = float (FP32 deviations) or double.
+// Cell fields, [ncomp][nc] or, where a pass reads the vector of another cell whole,
+// [nc][4] with a scalar that is read beside it. (A field that cells only read and
+// write for themselves is [3][nc]: the fourth component would be moved for
+// nothing in each subcycle.) R = float (FP32 deviations) or double.
 template <typename R>
 struct Cells {
     R *df_src, *df_dst;         // [19][nc] f_q - w_q
     R *j;                       // [nc][4] sum_q c_q f_q, rho - 1 at step start
     R *uprev;                   // [3][nc] u_f of the previous step
-    R *un;                      // [nc][4] u_f, rho - 1 of the current post-stream state (in fam's memory:
-                                // the cell-field pass has read it before the first spreading writes fam)
+    R *un;                      // [nc][4] u_f, rho - 1 of the current post-stream state (in fam's memory,
+                                // of 4 components: the cell-field pass has read it before the first
+                                // spreading writes fam)
     R *dudt;                    // [nc][4] Du_f/Dt, 0
     R *gradp;                   // [nc][4] grad P, 0
     R *epsp;                    // [nc] solid fraction 1 - eps_f of the current positions
-    R *fam;                     // [nc][4] -sum_p D F_am of the current subcycle, its eps_p
-    R *uf;                      // [nc][4] u_f re-evaluated with f_ext = eps_f f_b + fam, its eps_p
-    R *facc;                    // [nc][4] subcycle mean of f_ext, 0
+    R *fam;                     // [3][nc] -sum_p D F_am of the current subcycle
+    R *uf;                      // u_f re-evaluated with f_ext = eps_f f_b + fam: FP32 form [nc][4] with
+                                // eps_p, FP64 form [3][nc]
+    R *facc;                    // [3][nc] subcycle mean of f_ext
     R *curl;                    // [nc][4] curl of u_f at the subcycle start, 0 (lift only)
 };
 
@@ -178,8 +181,8 @@ constexpr int kGatherVariants = 5;
 template <typename R> void launch_stream_collide(const Desc &D, const Cells<R> &C, hipStream_t s);
 template <typename R> void launch_zero(R *p, int64_t n, hipStream_t s);
 template <typename R> void launch_to_double(const R *src, double *dst, int64_t n, hipStream_t s);
-template <typename R> void launch_vec4_to_double(const R *src, double *dst, int64_t nc, hipStream_t s);
 template <typename R> void launch_vec4_w_to_double(const R *src, double *dst, int64_t nc, hipStream_t s);
+template <typename R> void launch_vec4_to_double(const R *src, double *dst, int64_t nc, hipStream_t s);
 template <typename R> void launch_fluid_fraction(const R *src, double *dst, int64_t nc, hipStream_t s);
 template <typename R> void launch_from_double(const double *src, R *dst, int64_t n, hipStream_t s);
 template <typename R>

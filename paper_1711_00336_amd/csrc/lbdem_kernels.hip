@@ -188,6 +188,32 @@ __device__ __forceinline__ void load_vec4(const double *p, double v[4])
     v[3] = b.y;
 }
 
+// u_f of a cell with its eps_p: 4-vectors in the FP32 form, [3][nc] beside eps_p
+// in the FP64 form. There a 4-vector is two 16-byte stores 32 bytes apart, which
+// cost the gathers that write u_f in every subcycle more than the drag pass gains
+// by reading it whole: 128^3 cells with 64 thousand spheres, per subcycle, gathers
+// 118 us as [3][nc] and 128 as 4-vectors, drag 99 and 93 us; with lift gathers 159
+// and 174 us.
+__device__ __forceinline__ void store_uf(const Cells<float> &C, int64_t, int64_t c, const float u[3], float ep)
+{
+    store_vec4(C.uf + 4 * c, u[0], u[1], u[2], ep);
+}
+__device__ __forceinline__ void store_uf(const Cells<double> &C, int64_t nc, int64_t c, const double u[3], double)
+{
+#pragma unroll
+    for (int b = 0; b < 3; ++b) C.uf[b * nc + c] = u[b];
+}
+__device__ __forceinline__ void load_uf(const Cells<float> &C, int64_t, int64_t c, float v[4])
+{
+    load_vec4(C.uf + 4 * c, v);
+}
+__device__ __forceinline__ void load_uf(const Cells<double> &C, int64_t nc, int64_t c, double v[4])
+{
+#pragma unroll
+    for (int b = 0; b < 3; ++b) v[b] = C.uf[b * nc + c];
+    v[3] = C.epsp[c];
+}
+
 // ---------------------------------------------------------------------------
 // a1: moments of the post-stream PDFs (Eq. MacVel): rho - 1 = sum df,
 // j = sum c df (exact with deviations since sum_q w_q c_q = 0).
@@ -216,7 +242,10 @@ __global__ __launch_bounds__(kBlock) void k_moments(Desc D, Cells<R> C)
     const R u1 = (R)(((double)jy + 0.5 * e * D.p.fb[1]) / (rho * e));
     const R u2 = (R)(((double)jz + 0.5 * e * D.p.fb[2]) / (rho * e));
     store_vec4(C.un + 4 * c, u0, u1, u2, r);
-    if (D.p.use_lift) store_vec4(C.uf + 4 * c, u0, u1, u2, C.epsp[c]);
+    if (D.p.use_lift) {
+        const R uf[3] = {u0, u1, u2};
+        store_uf(C, nc, c, uf, C.epsp[c]);
+    }
 }
 
 // Neighbours x + c_q with the wall ghost rule: the mirrored in-domain cell;
@@ -310,9 +339,9 @@ __global__ __launch_bounds__(kBlock) void k_cellfields(Desc D, Cells<R> C)
         const double dtu = have_prev ? (un[b] - (double)C.uprev[b * nc + c]) : 0.0;
         du[b] = (R)(dtu + conv);
         C.uprev[b * nc + c] = (R)un[b];
+        C.facc[b * nc + c] = (R)0;
     }
     store_vec4(C.gradp + 4 * c, (R)gp[0], (R)gp[1], (R)gp[2]);
-    store_vec4(C.facc + 4 * c, (R)0, (R)0, (R)0);
     store_vec4(C.dudt + 4 * c, du[0], du[1], du[2]);
 }
 
@@ -341,7 +370,7 @@ __global__ __launch_bounds__(kBlock) void k_curl(Desc D, Cells<R> C)
         double sg;
         const int64_t nb = ghost(h, q, sg);
         R v[4];
-        load_vec4(C.uf + 4 * nb, v);
+        load_uf(C, nc, nb, v);
         const double u0 = sg * (double)v[0], u1 = sg * (double)v[1], u2 = sg * (double)v[2];
         s[0] += WQ(q) * (CY(q) * u2 - CZ(q) * u1);
         s[1] += WQ(q) * (CZ(q) * u0 - CX(q) * u2);
@@ -534,7 +563,7 @@ __global__ __launch_bounds__(kBlock) void k_part_am(Desc D, Cells<R> C)
                 if (LIFT) {
                     R o[4], uf[4];
                     load_vec4(C.curl + 4 * cell, o);
-                    load_vec4(C.uf + 4 * cell, uf);
+                    load_uf(C, D.g.nc, cell, uf);
 #pragma unroll
                     for (int b = 0; b < 3; ++b) {
                         U[b] += w * uf[b];
@@ -671,22 +700,23 @@ __device__ __forceinline__ void gather_value(const Parts &P, int p, double *v)
 }
 
 // fam = -sam and u_f = (j + (eps_f f_b + fam)/2) / (rho eps_f) of cell c with the
-// solid fraction ep; both keep the solid fraction for the passes that read them
+// solid fraction ep, which u_f keeps for the drag pass
 template <typename R>
 __device__ __forceinline__ void store_fam_uf(const Desc &D, const Cells<R> &C, int64_t c, R ep, const double *sam)
 {
-    R j[4], fam[3], uf[3];
+    const int64_t nc = D.g.nc;
+    R j[4], uf[3];
     load_vec4(C.j + 4 * c, j);
     const double e = 1.0 - (double)ep;
     const double rho = 1.0 + (double)j[3];
 #pragma unroll
     for (int b = 0; b < 3; ++b) {
-        fam[b] = (R)(-sam[b]);
-        const double fext = e * D.p.fb[b] + (double)fam[b];
+        const R fam = (R)(-sam[b]);
+        C.fam[b * nc + c] = fam;
+        const double fext = e * D.p.fb[b] + (double)fam;
         uf[b] = (R)(((double)j[b] + 0.5 * fext) / (rho * e));
     }
-    store_vec4(C.fam + 4 * c, fam[0], fam[1], fam[2], ep);
-    store_vec4(C.uf + 4 * c, uf[0], uf[1], uf[2], ep);
+    store_uf(C, nc, c, uf, ep);
 }
 
 template <typename R, int MODE>
@@ -700,16 +730,13 @@ __device__ __forceinline__ void gather_store(const Desc &D, const Cells<R> &C, i
         C.epsp[c] = (R)s[0];
         store_fam_uf<R>(D, C, c, (R)s[0], s + 1);
     } else if (MODE == MODE_FD) {
-        R fam[4], facc[4];
-        load_vec4(C.fam + 4 * c, fam);
-        load_vec4(C.facc + 4 * c, facc);
-        const double e = 1.0 - (double)fam[3];
+        const int64_t nc = D.g.nc;
+        const double e = 1.0 - (double)C.epsp[c];
 #pragma unroll
         for (int b = 0; b < 3; ++b) {
-            const double fext = e * D.p.fb[b] + (double)fam[b] - s[b];
-            facc[b] = (R)((double)facc[b] + fext * D.p.dt_int);
+            const double fext = e * D.p.fb[b] + (double)C.fam[b * nc + c] - s[b];
+            C.facc[b * nc + c] = (R)((double)C.facc[b * nc + c] + fext * D.p.dt_int);
         }
-        store_vec4(C.facc + 4 * c, facc[0], facc[1], facc[2]);
         if (c == 0) {  // requests that have been served, before this subcycle's substeps make new ones
 #pragma unroll
             for (int t = 0; t < 3; ++t)
@@ -726,7 +753,7 @@ __device__ __forceinline__ void gather_store(const Desc &D, const Cells<R> &C, i
             const double rho = 1.0 + (double)j[3];
 #pragma unroll
             for (int b = 0; b < 3; ++b) uf[b] = (R)(((double)j[b] + 0.5 * ef * D.p.fb[b]) / (rho * ef));
-            store_vec4(C.uf + 4 * c, uf[0], uf[1], uf[2], (R)s[0]);
+            store_uf(C, D.g.nc, c, uf, (R)s[0]);
         }
     }
 }
@@ -1002,7 +1029,7 @@ __global__ __launch_bounds__(kBlock) void k_part_drag(Desc D, Cells<R> C, int re
                 const int64_t cell = cidx(D.g, cx, cy, cz);
                 const R w = (R)(st.w[0][ox] * st.w[1][oy] * sel3(st.w[2], oz));
                 R u4[4], g4[4];
-                load_vec4(C.uf + 4 * cell, u4);
+                load_uf(C, D.g.nc, cell, u4);
                 load_vec4(C.gradp + 4 * cell, g4);
 #pragma unroll
                 for (int b = 0; b < 3; ++b) {
@@ -1029,7 +1056,10 @@ __global__ __launch_bounds__(kBlock) void k_part_drag(Desc D, Cells<R> C, int re
 //
 // The cell fields come as 4-vectors, (u_f, eps_p) and grad P for the drag, Du/Dt,
 // u_f and the curl for the added mass with lift: two or three 16-byte accesses
-// per cell, from memory and from LDS, instead of seven or nine 4-byte ones.
+// per cell instead of seven or nine 4-byte ones (but see store_uf). In LDS the
+// drag keeps all four components; the added mass the three that it reads, which
+// lets three workgroups of the FP64 form share a CU, not two (128^3 cells, 64
+// thousand spheres: 117 us against 136).
 enum { PASS_DRAG = 1, PASS_AML = 2 };
 
 template <typename R, int PASS, int TX, int TY, int TZ, int NT>
@@ -1039,7 +1069,8 @@ __global__ __launch_bounds__(NT) void k_part_tile(Desc D, Cells<R> C, int record
     constexpr int NF = PASS == PASS_DRAG ? 2 : 3;  // 4-vectors per cell
     constexpr int NR = TY * TZ;
     static_assert(NR <= 64, "rows of one tile are scanned by one wavefront");
-    __shared__ __align__(16) R cv[NF][NHC][4];
+    constexpr int NC = PASS == PASS_DRAG ? 4 : 3;  // components kept
+    __shared__ __align__(16) R cv[NF][NHC][NC];
     __shared__ int rp[NR + 1], rsrc[NR];
 
     const int tid = threadIdx.x;
@@ -1078,7 +1109,8 @@ __global__ __launch_bounds__(NT) void k_part_tile(Desc D, Cells<R> C, int record
         if (rp[NR] == 0) return;
     }
     // halo cell fields
-    const R *field[3] = {PASS == PASS_DRAG ? C.uf : C.dudt, PASS == PASS_DRAG ? C.gradp : C.uf, C.curl};
+    constexpr int FU = PASS == PASS_DRAG ? 0 : 1;  // place of u_f
+    const R *field[3] = {C.dudt, C.gradp, C.curl};
     for (int hc = tid; hc < NHC; hc += NT) {
         const int hx = hc % HX, hy = (hc / HX) % HY, hz = hc / (HX * HY);
         R v[NF][4];
@@ -1088,7 +1120,10 @@ __global__ __launch_bounds__(NT) void k_part_tile(Desc D, Cells<R> C, int record
             const int gz = stencil_coord(z0, hz - 1, n2, D.g.per[2]);
             const int64_t cell = cidx(D.g, gx, gy, gz);
 #pragma unroll
-            for (int f = 0; f < NF; ++f) load_vec4(field[f] + 4 * cell, v[f]);
+            for (int f = 0; f < NF; ++f) {
+                if (f == FU) load_uf(C, D.g.nc, cell, v[f]);
+                else load_vec4(field[f] + 4 * cell, v[f]);
+            }
         } else {
 #pragma unroll
             for (int f = 0; f < NF; ++f)
@@ -1096,7 +1131,12 @@ __global__ __launch_bounds__(NT) void k_part_tile(Desc D, Cells<R> C, int record
                 for (int t = 0; t < 4; ++t) v[f][t] = (R)0;
         }
 #pragma unroll
-        for (int f = 0; f < NF; ++f) store_vec4(cv[f][hc], v[f][0], v[f][1], v[f][2], v[f][3]);
+        for (int f = 0; f < NF; ++f) {
+            if constexpr (NC == 4) store_vec4(cv[f][hc], v[f][0], v[f][1], v[f][2], v[f][3]);
+            else
+#pragma unroll
+                for (int t = 0; t < 3; ++t) cv[f][hc][t] = v[f][t];
+        }
     }
     __syncthreads();
 
@@ -1133,7 +1173,10 @@ __global__ __launch_bounds__(NT) void k_part_tile(Desc D, Cells<R> C, int record
 #pragma unroll
                     for (int f = 0; f < NF; ++f) {
                         R v[4];
-                        load_vec4(cv[f][hc], v);
+                        if constexpr (NC == 4) load_vec4(cv[f][hc], v);
+                        else
+#pragma unroll
+                            for (int t = 0; t < 3; ++t) v[t] = cv[f][hc][t];
 #pragma unroll
                         for (int t = 0; t < (PASS == PASS_DRAG && f == 0 ? 4 : 3); ++t) acc[f][t] += w * v[t];
                     }
@@ -2496,9 +2539,7 @@ __device__ __forceinline__ void collide_cell(const Desc &D, const Cells<R> &C, i
     }
     const R one = (R)1;
     const R rho = one + r;
-    R fa[4];
-    load_vec4(C.facc + 4 * c, fa);
-    const R fx = fa[0], fy = fa[1], fz = fa[2];
+    const R fx = C.facc[c], fy = C.facc[nc + c], fz = C.facc[2 * nc + c];
     const R half = (R)0.5;
     const R ux = (jx + half * fx) / rho, uy = (jy + half * fy) / rho, uz = (jz + half * fz) / rho;
     const R eps = one - C.epsp[c];
