@@ -278,8 +278,7 @@ lbdem_status lbdem_load_state(lbdem_domain_t h, const void *blob, size_t size);
  * particle pass (first subcycle; without lift the later subcycles' added
  * mass runs inside class 10, or 9 when fused), 4 drag/pressure particle pass, 5 added-mass
  * spreading, 6 drag spreading and f_acc, 7 volume fraction (+ next
- * added-mass spreading), 8 Verlet list build (inside class 9 where the
- * fused pass does it), 9 DEM contact/lubrication
+ * added-mass spreading), 8 Verlet list build, 9 DEM contact/lubrication
  * forces, 10 DEM integration, 11 particle binning and reordering, 12
  * subcycle u_f and its curl (lift only). E_INVALID for a class outside
  * 0..12. */

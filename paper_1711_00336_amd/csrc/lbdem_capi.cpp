@@ -668,10 +668,10 @@ void enqueue_step(lbdem_domain_t h)
     for (int k = 0; k < nint; ++k) {
         const int last_sub = k == nint - 1;
         // the lists before the drag spreading, which clears the requests served
-        if (!dem_builds_lists(h->desc())) launch_cls(h, 8, [&] { launch_nlist<R>(h->desc(), s); });
+        launch_cls(h, 8, [&] { launch_nlist<R>(h->desc(), s); });
         launch_cls(h, 4, [&] { launch_part_drag<R>(h->desc(), C, last_sub, s); });
         Desc fd = h->desc();
-        fd.clear = dem_served_requests(fd, k);
+        fd.clear = k == 0 ? 3 : 1;
         launch_cls(h, 6, [&] { launch_gather_fd<R>(fd, C, s); });
         for (int sub = 0; sub < h->phys.n_dem; ++sub) {
             const int last_dem = sub == h->phys.n_dem - 1;

@@ -108,8 +108,7 @@ struct Parts {
     int *nlist, *nnb;
     int nbr;                    // list capacity per particle (sized from the density and reach)
     double *xbuild;
-    int *need;                  // [0] 1: rebuild the lists before the next DEM substep ([2] after every
-                                // second subcycle where the fused pass builds them);
+    int *need;                  // [0] 1: rebuild the lists before the next DEM substep;
                                 // [1] 1: reorder the slots at the next step's start
     void *pk, *pk2;             // DemRec<R> by slot (+ those of the odd substeps when fused)
 };
@@ -202,8 +201,6 @@ template <typename R> void launch_dem_force(const Desc &D, const Cells<R> &C, hi
 // between pk and pk2 by substep parity)
 bool dem_substep_fused(const Desc &D);
 bool dem_subcycle_single(const Desc &D);
-bool dem_builds_lists(const Desc &D);                 // whether that pass rebuilds the lists itself
-int dem_served_requests(const Desc &D, int k);        // Desc::clear of subcycle k
 template <typename R>
 void launch_dem_substep_fused(const Desc &D, const Cells<R> &C, int k, int sub, hipStream_t s);
 void launch_reorder(const Desc &D, hipStream_t s);    // slots into list order if due

@@ -739,7 +739,7 @@ __device__ __forceinline__ void gather_store(const Desc &D, const Cells<R> &C, i
         }
         if (c == 0) {  // requests that have been served, before this subcycle's substeps make new ones
 #pragma unroll
-            for (int t = 0; t < 3; ++t)
+            for (int t = 0; t < 2; ++t)
                 if (D.clear & (1 << t)) D.pt.need[t] = 0;
         }
     } else {
@@ -1559,10 +1559,8 @@ __device__ __forceinline__ void load_sphere(const DemRec<R> *pk, int64_t i, doub
     d = b.y;
 }
 
-// the list of slot i, by one wavefront; lds: 2 kListLds ints of its own. Positions
-// come from the records pk of the subcycle's start: the state arrays may already
-// hold another workgroup's new ones. Neighbours beyond the capacity raise
-// FLAG_NLIST if `judge`.
+// the list of slot i, by one wavefront; lds: 2 kListLds ints of its own. Neighbours
+// beyond the capacity raise FLAG_NLIST if `judge`.
 template <typename R>
 __device__ __forceinline__ void build_list(const Desc &D, const DemRec<R> *pk, int64_t i, int lane, int *lds,
                                            bool judge)
@@ -1688,12 +1686,7 @@ template <typename R> __global__ __launch_bounds__(kBlock) void k_nlist(Desc D, 
 enum : int {
     SUB_LAST = 1,  // du_p/dt, kernel stencil of the new position, bin count, list check
     SUB_AM = 2,    // the next subcycle's added-mass force (without lift, except before a step's end)
-    SUB_END = 4,   // the last subcycle of a step: ask for a reordering ahead of the next step
-    // where the fused pass builds the lists: SUB_REQ2 if the request to read is
-    // need[2] and the one to make need[0] (every second subcycle), SUB_REQ0 the
-    // other way round
-    SUB_REQ0 = 8,
-    SUB_REQ2 = 16
+    SUB_END = 4    // the last subcycle of a step: ask for a reordering ahead of the next step
 };
 
 // One semi-implicit Euler substep of particle i (R5: u and omega first,
@@ -1788,7 +1781,7 @@ __device__ __forceinline__ void integrate_particle(const Desc &D, const Cells<R>
     // reordering (and with it the rebuild) is asked for a little earlier, so that
     // rebuilds fall on step starts, after a reordering.
     const double limit2 = 0.25 * D.p.vskin * D.p.vskin;
-    if (ahead2 > limit2) P.need[sub & SUB_REQ0 ? 2 : 0] = P.need[1] = 1;
+    if (ahead2 > limit2) P.need[0] = P.need[1] = 1;
     else if ((sub & SUB_END) && ahead2 > 0.92 * 0.92 * limit2) P.need[1] = 1;
     atomicAdd(&D.b.cnt[particle_cell(D.g, x[0], x[1], x[2])], 1);
     // the stencil of a position outside the domain or not finite is not taken
@@ -1845,8 +1838,8 @@ __device__ __forceinline__ bool dem_pair(const Desc &D, const PV &pi, const PV &
 }
 
 constexpr int kRun = 2;  // entries per lane and run, several lanes per particle
-constexpr int kDemLds = 4096;  // bytes of LDS per wavefront: 64 records' pieces, a run's terms or a list being built
-static_assert(2 * kListLds * sizeof(int) <= kDemLds && 64 * 4 * sizeof(uint4) <= kDemLds, "");
+constexpr int kDemLds = 4096;  // bytes of LDS per wavefront: 64 records' pieces or a run's terms
+static_assert(64 * 4 * sizeof(uint4) <= kDemLds, "");
 
 // one lane per particle: the slots of entry t of four groups of 16 lists, and the
 // calling lane's piece q of those four records (see below)
@@ -2046,24 +2039,9 @@ __device__ __forceinline__ void dem_particle(const Desc &D, const DemRec<R> *src
 // alternate between the two record buffers (odd: from pk2 to pk), reading the
 // records of the substep's start and writing the integrated ones to the other
 // buffer, so that no thread sees another's update.
-// LISTS: where a rebuild is due, a workgroup first builds the lists of its own
-// particles, which nobody else reads (a launch of its own, idle most subcycles,
-// took 4 us of them: 32x32x64 cells with 64 particles, ten steps 4.74 -> 4.50 ms).
-template <typename R>
-__device__ __forceinline__ void dem_lists(const Desc &D, int sub, const DemRec<R> *pk, int64_t i0, int n, char *lds)
-{
-    // (need[] does not change during the pass: the condition is uniform)
-    if (D.pt.need[sub & SUB_REQ2 ? 2 : 0] == 0) return;
-    if (!halted(D))
-        for (int k = threadIdx.x >> 6; k < n && i0 + k < D.pt.np; k += blockDim.x >> 6)
-            build_list<R>(D, pk, i0 + k, threadIdx.x & 63, (int *)lds, true);
-    __syncthreads();
-}
-
 // (4 waves per SIMD in the FP32 form with one lane per particle, which needs 129
 // registers otherwise)
-// (LISTS: the instance that can build lists; the code alone costs the others 1 %)
-template <typename R, int G, bool FUSE, typename Off, bool LISTS>
+template <typename R, int G, bool FUSE, typename Off>
 __global__ __launch_bounds__(kBlock, sizeof(R) == 4 && G == 1 ? 4 : 1) void k_dem_force(Desc D, Cells<R> C, int sub, int odd)
 {
     __shared__ __align__(16) char lds[kBlock / 64][kDemLds];
@@ -2071,7 +2049,6 @@ __global__ __launch_bounds__(kBlock, sizeof(R) == 4 && G == 1 ? 4 : 1) void k_de
     const Parts &P = D.pt;
     DemRec<R> *pk = (DemRec<R> *)P.pk, *pk2 = (DemRec<R> *)P.pk2;
     const int64_t v = gidx();
-    if constexpr (LISTS) dem_lists<R>(D, sub, pk, (v - threadIdx.x) / G, kBlock / G, T);
     int64_t i = v / G;
     const int l = (int)(v % G);
     // a wavefront with particles keeps all its lanes (they load for each other);
@@ -3003,22 +2980,22 @@ static inline int dem_lanes(const Desc &D)
     if (n > 131072 || mean < 6.0) return 1;
     return n <= 32768 && mean >= 12.0 ? 8 : 2;
 }
-template <typename R, bool FUSE, bool LISTS>
+template <typename R, bool FUSE>
 static void launch_dem(const Desc &D, const Cells<R> &C, int sub, int odd, hipStream_t s)
 {
     if (D.pt.np == 0) return;
     const int g = dem_lanes(D);
     const dim3 grid(nblocks(D.pt.np * g)), blk(kBlock);
-    if (g == 8) hipLaunchKernelGGL((k_dem_force<R, 8, FUSE, uint32_t, LISTS>), grid, blk, 0, s, D, C, sub, odd);
-    else if (g == 2) hipLaunchKernelGGL((k_dem_force<R, 2, FUSE, uint32_t, LISTS>), grid, blk, 0, s, D, C, sub, odd);
+    if (g == 8) hipLaunchKernelGGL((k_dem_force<R, 8, FUSE, uint32_t>), grid, blk, 0, s, D, C, sub, odd);
+    else if (g == 2) hipLaunchKernelGGL((k_dem_force<R, 2, FUSE, uint32_t>), grid, blk, 0, s, D, C, sub, odd);
     else if ((uint64_t)D.pt.np * sizeof(DemRec<R>) <= UINT32_MAX)
-        hipLaunchKernelGGL((k_dem_force<R, 1, FUSE, uint32_t, LISTS>), grid, blk, 0, s, D, C, sub, odd);
+        hipLaunchKernelGGL((k_dem_force<R, 1, FUSE, uint32_t>), grid, blk, 0, s, D, C, sub, odd);
     else
-        hipLaunchKernelGGL((k_dem_force<R, 1, FUSE, uint64_t, LISTS>), grid, blk, 0, s, D, C, sub, odd);
+        hipLaunchKernelGGL((k_dem_force<R, 1, FUSE, uint64_t>), grid, blk, 0, s, D, C, sub, odd);
 }
 template <typename R> void launch_dem_force(const Desc &D, const Cells<R> &C, hipStream_t s)
 {
-    launch_dem<R, false, false>(D, C, 0, 0, s);
+    launch_dem<R, false>(D, C, 0, 0, s);
 }
 bool dem_substep_fused(const Desc &D)
 {
@@ -3034,31 +3011,16 @@ bool dem_subcycle_single(const Desc &D)
 {
     return dem_substep_fused(D) && D.p.n_dem > 1 && D.pt.np <= kBlock && dem_lanes(D) == 1;
 }
-// Whether the fused pass builds the lists itself: with one DEM substep, whose launch
-// is all that a subcycle has (in passes with more of them the code costs more than
-// the launch of 4 us that it saves: single-launch subcycles of impact
-// 1.49 -> 1.56 ms with it). The pass's two request flags alternate from subcycle to
-// subcycle, and must from step to step.
-bool dem_builds_lists(const Desc &D)
-{
-    return dem_substep_fused(D) && D.p.n_int % 2 == 0 && D.p.n_dem == 1;
-}
-int dem_served_requests(const Desc &D, int k)
-{
-    return (k == 0 ? 2 : 0) | (dem_builds_lists(D) && k % 2 == 0 ? 4 : 1);
-}
 template <typename R>
 void launch_dem_substep_fused(const Desc &D, const Cells<R> &C, int k, int sub, hipStream_t s)
 {
     if (D.pt.np == 0) return;
     const bool single = dem_subcycle_single(D);
     const int f = sub_flags(D, single || sub == D.p.n_dem - 1, k == D.p.n_int - 1);
-    if (dem_builds_lists(D))
-        launch_dem<R, true, true>(D, C, f | (k % 2 ? SUB_REQ2 : SUB_REQ0), 0, s);
-    else if (single)
+    if (single)
         hipLaunchKernelGGL(k_dem_subcycle<R>, dim3(1), dim3((unsigned)((D.pt.np + 63) / 64 * 64)), 0, s, D, C, f);
     else
-        launch_dem<R, true, false>(D, C, f, sub & 1, s);
+        launch_dem<R, true>(D, C, f, sub & 1, s);
 }
 bool dem_sorts_lengths(const Desc &D) { return sort_lengths(D); }
 // slots into the order of the sorted list, or the blocked one, if due
@@ -3078,7 +3040,10 @@ template <typename R> void launch_nlist(const Desc &D, hipStream_t s, bool judge
 {
     if (D.pt.np <= 0) return;
     // few workgroups, as most launches find nothing to do (one wavefront per
-    // particle at a build)
+    // particle at a build). Idle, the launch is 1 to 3 % of a step of one DEM
+    // substep per subcycle; built by the DEM pass instead, up to 64 lists after
+    // one another per wavefront, the lists of 13.8 k spheres due every third
+    // subcycle made it 0.99 ms long, not 0.77
     const int64_t nb = (D.pt.np + kBlock / 64 - 1) / (kBlock / 64);
     hipLaunchKernelGGL(k_nlist<R>, dim3((unsigned)(nb < 2048 ? nb : 2048)), dim3(kBlock), 0, s, D, judge);
 }

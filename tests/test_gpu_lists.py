@@ -115,12 +115,11 @@ def _list_builds(u, n_int, steps):
 @pytest.mark.parametrize("eps,h_c", [(0.05, 0.5), (0.1, 0.5), (0.1, 1.0)])
 @pytest.mark.parametrize("precision", ["fp64", "fp32dev"])
 def test_lists_built_at_odd_subcycles(L, n_int, speed, eps, h_c, precision):
-    """Lists built inside the pass of one DEM substep, at odd and at even
-    subcycles in mid-step: heavy spheres with soft contacts in nearly straight
-    diagonal flight, half of them the other way, so that pairs come within
-    reach between the builds. One, two and eight lanes per particle. Against
-    the oracle (the bars of free-running steps) and, bit for bit, against
-    lists built by their own launch."""
+    """Lists built in mid-step, at odd and at even subcycles: heavy spheres
+    with soft contacts in nearly straight diagonal flight, half of them the
+    other way, so that pairs come within reach between the builds. One, two and
+    eight lanes per particle. Against the oracle (the bars of free-running
+    steps) and, bit for bit, against separate force and integration passes."""
     from tests.parity_util import compare_states
     from oracle import oracle as O
     n, steps = (8, 9, 10), 3 if n_int == 10 else 4
