@@ -2967,18 +2967,27 @@ void launch_diag(const Desc &D, const Cells<R> &C, const R *df, double *partials
 // Lanes per particle of the DEM pass. Fewer lanes are less work in all (the sums
 // through LDS, the particle's record and, fused, its integration are then
 // shared by more entries); more lanes fill the chip and shorten the chain of
-// dependent loads, as long as each has entries enough. A coupled step, fused,
-// with 1 / 2 / 4 / 8 / 16 lanes: 18,775 FP64 spheres (26 list entries, 500
-// substeps) 19.9 / 14.7 / 11.5 / 10.1 / 11.6 ms; 49,536 (30 entries, 100
-// substeps) 4.70 / 4.09 / 4.10 / 4.33 / 5.53 ms; 42,808 (3.5 entries, 40
-// substeps) 3.86 / 3.86 / 3.85 / 4.58 / 5.76 ms; 64 (none, 100 substeps) 4.85 /
-// 4.91 / 5.04 / 5.24 / 5.32 ms.
+// dependent loads, as long as each has entries enough and all wavefronts are
+// resident at once: three on each of 1024 SIMDs, 98,304 particles with two lanes
+// and 24,576 with eight.
+// A step of 4 x 10 substeps on a jittered lattice, FP64, ms with 1 / 2 / 8 lanes:
+//   list entries about    9                    14                   36
+//    4,096 particles   0.56 / 0.48 / 0.45   0.90 / 0.70 / 0.52   1.29 / 0.95 / 0.56
+//   24,389             0.65 / 0.55 / 0.58   0.99 / 0.77 / 0.71   1.39 / 1.03 / 0.78
+//   32,768             0.66 / 0.57 / 0.70   1.00 / 0.78 / 0.87   1.41 / 1.05 / 0.97
+//   50,653             0.73 / 0.68 / 0.94   1.06 / 0.96 / 1.20   1.47 / 1.29 / 1.33
+//   97,336             0.96 / 0.89 / 1.43   1.41 / 1.26 / 1.87   1.93 / 1.66 / 2.07
+//  110,592 (103,823)   0.98 / 1.08 / 1.60   1.43 / 1.57 / 2.10   1.84 / 2.11 / 2.23
+// (FP32 within 10 % of these ratios.) With fewer than six entries the lanes find
+// little to share (42,808 particles with 3.5: 3.86 / 3.86 / 4.58). Up to 256
+// particles one lane means a single launch per subcycle; crowded ones are still
+// better off with eight: 216 with 33 entries, 4 x 50 substeps, 7.0 / 3.7 / 1.8.
 static inline int dem_lanes(const Desc &D)
 {
     const int64_t n = D.pt.np;
     const double r = D.p.reach_max, mean = (double)n / (double)D.g.nc * (4.0 / 3.0) * M_PI * r * r * r;
-    if (n > 131072 || mean < 6.0) return 1;
-    return n <= 32768 && mean >= 12.0 ? 8 : 2;
+    if (n > 98304 || mean < 6.0) return 1;
+    return mean >= 12.0 && n <= (mean < 20.0 ? 24576 : 32768) ? 8 : 2;
 }
 template <typename R, bool FUSE>
 static void launch_dem(const Desc &D, const Cells<R> &C, int sub, int odd, hipStream_t s)
