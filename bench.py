@@ -130,7 +130,9 @@ def kernel_bytes(case, nlist, dem_order=0, fused=False):
     operation must read and write once (re-reads of neighbour cells or
     particles, which a cache can serve, are not counted). rs is the cell
     storage size (4 B FP32-deviation, 8 B FP64); ws the stored kernel-weight
-    size (4 B / 8 B); particle state is FP64.
+    size (4 B / 8 B); particle state is FP64. (nlist, dem_force, integrate and
+    bins are those of a step that looks neighbours up by label and permutes the
+    particles every subcycle; launch_bytes has the present ones.)
 
       stream_collide  per cell 19 PDF reads + 19 writes + eps_p + f_acc(3)  42 rs
       moments         per cell 19 PDFs + eps_p read, rho, j, u_f written    27 rs
@@ -197,30 +199,39 @@ def kernel_bytes(case, nlist, dem_order=0, fused=False):
 
 
 def launch_bytes(case, nlist, dem_order, fused):
-    """kernel_bytes with the classes that slots fixed between list rebuilds and
-    the records of both storage forms make cheaper:
+    """The figures that launches are rated with: kernel_bytes, with the classes
+    put right that slots fixed between list rebuilds and the records of both
+    storage forms (rec = 64 B FP32, 96 B FP64) make cheaper:
 
       nlist           nothing but the request is read where no rebuild is due    0
       dem_force       with the integration: per particle list length, record,
       (fused)         u, F_const, x_start read, u and the new record written,
                       L slots read; in the FP32 form also rho
-                                100 B [+ 8] + 2 records (64 or 96 B) + 4 L B
+                                                      100 B [+ 8] + 2 rec + 4 L B
                       a lone substep also leaves x, a, the stencil and F_am and
                       reads the build position instead of x_start, per cell
                       Du/Dt                            84 B + 9 ws and 4 rs more
+      dem_force       per particle list length, record, L slots read, F, T
+                      written                                 52 B + rec + 4 L B
+      integrate       per particle x, u, omega, F_const, F, T, d, rho, x_start
+                      read, x, u, omega and the record written        256 B + rec
       bins            per particle position's cell, list entry (12 B) and its
                       order by id (12 B); per cell count, scan, offsets (20 B)
     """
     kb = kernel_bytes(case, nlist, dem_order, fused)
     n = int(case.particles.n)
     fp32 = case.params.precision == "fp32dev"
+    rec = 64 if fp32 else 96
     kb["nlist"] = 0
     kb["bins"] = n * 24 + int(np.prod(case.params.n)) * 20
     if fused:
         rs = ws = 4 if fp32 else 8
-        kb["dem_force"] = int(n * ((236 if fp32 else 292) + 4 * nlist))
+        kb["dem_force"] = int(n * (100 + (8 if fp32 else 0) + 2 * rec + 4 * nlist))
         if case.params.n_dem == 1:
             kb["dem_force"] += n * (84 + 9 * ws) + int(np.prod(case.params.n)) * 4 * rs
+    else:
+        kb["dem_force"] = int(n * (52 + rec + 4 * nlist))
+        kb["integrate"] = n * (256 + rec)
     return kb
 
 
