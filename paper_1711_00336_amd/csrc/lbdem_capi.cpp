@@ -77,7 +77,7 @@ struct lbdem_domain {
     int *cnt = nullptr, *start = nullptr, *list = nullptr, *bsum = nullptr, *loc = nullptr;
     int64_t list_cap = 0;
     int64_t nlist_rows = 0;     // particle rows the Verlet-list buffer holds
-    // blocked processing order of the DEM force pass
+    // blocked slot order
     Order ord{};
     int64_t ord_rows_cap = 0;
     // particles
@@ -326,10 +326,7 @@ void update_search(lbdem_domain_t h)
     if (P.rbin > 8) throw std::runtime_error("interaction reach d_max + h_c exceeds the 8-cell search limit");
 }
 
-// Verlet-list capacity per particle: twice the mean number of neighbours
-// within the list reach (d_max + h_c + skin) at the domain's mean particle
-// density, plus 24; a particle with more neighbours raises FLAG_NLIST
-// block shape of the DEM processing order; (re)allocates the row arrays
+// block shape of the blocked slot order; (re)allocates the row arrays
 void set_order_shape(lbdem_domain_t h, int bx, int by, int bz)
 {
     Order &O = h->ord;
@@ -350,6 +347,10 @@ void set_order_shape(lbdem_domain_t h, int bx, int by, int bz)
     }
 }
 
+// Verlet-list capacity per particle: twice the mean number of neighbours
+// within the list reach (d_max + h_c + skin) at the domain's mean particle
+// density, plus 24; a particle with more neighbours raises FLAG_NLIST when a
+// step builds its list
 void ensure_lists(lbdem_domain_t h)
 {
     Parts &P = h->pt;

@@ -180,8 +180,8 @@ constexpr int kGatherVariants = 5;
 template <typename R> void launch_stream_collide(const Desc &D, const Cells<R> &C, hipStream_t s);
 template <typename R> void launch_zero(R *p, int64_t n, hipStream_t s);
 template <typename R> void launch_to_double(const R *src, double *dst, int64_t n, hipStream_t s);
-template <typename R> void launch_vec4_w_to_double(const R *src, double *dst, int64_t nc, hipStream_t s);
 template <typename R> void launch_vec4_to_double(const R *src, double *dst, int64_t nc, hipStream_t s);
+template <typename R> void launch_vec4_w_to_double(const R *src, double *dst, int64_t nc, hipStream_t s);
 template <typename R> void launch_fluid_fraction(const R *src, double *dst, int64_t nc, hipStream_t s);
 template <typename R> void launch_from_double(const double *src, R *dst, int64_t n, hipStream_t s);
 template <typename R>

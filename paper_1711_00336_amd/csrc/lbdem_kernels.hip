@@ -649,12 +649,13 @@ __device__ __forceinline__ void gather_cell(const Desc &D, int i, int j, int k, 
 // ---------------------------------------------------------------------------
 // LDS-tiled gather. A workgroup owns a TX x TY x (TZ*CZ) tile of cells, each
 // thread CZ consecutive cells along z. It counts the particles of the tile's
-// halo bins (the tile widened by one cell, wrapped on periodic axes), lists
-// their slots in LDS (a bin's particles are one contiguous slot range, listed
-// by the thread that owns the bin), stages their stencils and values into
-// LDS one entry per thread (independent, coalesced loads), and then every cell
-// sums the particles of its own 3x3x3 bins from LDS, in the order
-// (dz, dy, dx, slot) whatever the tile shape. Tiles whose halo holds more
+// halo bins (the tile widened by one cell, wrapped on periodic axes), notes
+// their places in the sorted slot list in LDS (a bin is one contiguous range of
+// that list, noted by the thread that owns the bin), stages their stencils and
+// values into LDS one entry per thread (gathers through the list, independent
+// of each other; slots are close to list order), and then every cell sums the
+// particles of its own 3x3x3 bins from LDS, in the order (dz, dy, dx, insertion
+// index) whatever the tile shape and the slots. Tiles whose halo holds more
 // than KMAX particles are staged in runs of halo planes; only where one plane
 // exceeds KMAX does the tile fall back to the per-cell global gather. (Half-cell
 // spheres at solid fraction 0.3, 4.6 per cell, 16^3 cells, FP64: 47 us
@@ -1083,7 +1084,7 @@ __global__ __launch_bounds__(NT) void k_part_tile(Desc D, Cells<R> C, int record
     const int xe = min(x0 + TX, n0);
     const int lx = xe - x0 + 1, ly = min(y0 + TY, n1) - y0 + 1, lz = min(z0 + TZ, n2) - z0 + 1;
 
-    // own particles: one slot range per row of bins
+    // own particles: one range of the slot list per row of bins
     if (tid < 64) {
         int cnt = 0, src = 0;
         if (tid < NR) {
@@ -1490,7 +1491,7 @@ template <typename R> __device__ __forceinline__ void load_spin(const DemRec<R> 
 __device__ __forceinline__ bool halted(const Desc &D) { return *(volatile const int *)D.flags != 0; }
 
 // whether this step starts with a reordering of the slots (need[1] is set
-// during a step and cleared by the first list pass of the next)
+// during a step and cleared by the first drag spreading of the next)
 __device__ __forceinline__ bool reorder_due(const Desc &D) { return D.pt.need[1] != 0 && !halted(D); }
 
 __device__ __forceinline__ void min_image(const Geo &g, double dx[3])
@@ -1810,7 +1811,7 @@ __device__ __forceinline__ void integrate_particle(const Desc &D, const Cells<R>
 // (4e-4 per sphere in a dense suspension), and evaluated inline the whole
 // wavefront would step through the contact code for them. Lubrication, contacts
 // and the walls are summed apart and added at the end. The pass is bound by
-// FP64 instruction issue (71 % of the SIMD cycles without the integration, 58 %
+// FP64 instruction issue (66 % of the SIMD cycles without the integration, 59 %
 // with it) and by the latency of the record gathers. Forces and integration of a
 // substep of 3.17 M dense spheres (29.6 list entries each): 1.28 ms as two
 // passes with a lane per record, 0.78 ms. Not kept: non-temporal loads of the
@@ -2266,8 +2267,11 @@ __global__ __launch_bounds__(kBlock) void k_scan_block(Desc D, int both)
     }
     // The last workgroup to get here scans the block sums (both levels in one
     // launch). Sums and count go through atomics at device scope, which all XCDs
-    // see at once; the sum's has returned before the count's is issued. (Release
-    // order instead writes the XCD's whole L2 back per workgroup: 88 us on 128^3 cells.)
+    // see at once; the sum's has returned before the count's is issued. That the
+    // two are seen in this order is the hardware's (an atomic that has returned
+    // its old value is done where every XCD looks), not the memory model's, which
+    // asks for release order; that writes the XCD's whole L2 back per workgroup:
+    // 88 us on 128^3 cells.
     __shared__ int last;
     if (threadIdx.x == 0) {
         int old = __hip_atomic_exchange(D.b.bsum + blockIdx.x, btot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -2331,7 +2335,7 @@ __global__ __launch_bounds__(1024) void k_scan_top(int *bsum, int nb, int *total
     if (threadIdx.x == 1023) *total = sh[1023];
 }
 
-// slot range start of bin c from the block-local prefix and the block offset
+// start of bin c in the slot list from the block-local prefix and the block offset
 __device__ __forceinline__ int bin_start(const Bins &B, int64_t c)
 {
     return B.loc[c] + B.bsum[c / kScanPerBlock];

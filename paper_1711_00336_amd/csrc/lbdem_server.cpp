@@ -69,10 +69,11 @@ lbdem_status sfail(lbdem_status st, const std::string &m)
     return st;
 }
 
-// device bytes of one domain: two PDF buffers and 30 field components per
-// cell in the storage precision, bins, per-particle state, and the Verlet
-// lists (capacity twice the mean neighbour count within d_max + h_c + 0.25,
-// plus 24 entries, as the domain sizes them)
+// device bytes of one domain, from above: two PDF buffers and 30 field
+// components per cell in the storage precision (26 or 27 are held, 4 more with lift),
+// bins, per-particle state, and the Verlet lists (capacity twice the mean
+// neighbour count within d_max + h_c + 0.25, plus 28 entries; a domain sizes
+// them with 0.1 and 24)
 size_t footprint_of(const lbdem_params &p, int64_t np, double dmax)
 {
     const size_t nc = (size_t)p.n[0] * p.n[1] * p.n[2];
