@@ -2641,7 +2641,10 @@ __global__ __launch_bounds__(kBlock) void k_diag(Desc D, Cells<R> C, const R *df
         acc[6] += ub2 / e;
         acc[7] = fmax(acc[7], sqrt(ub0 * ub0 + ub1 * ub1 + ub2 * ub2));
     }
-    for (int64_t i = gidx(); i < np; i += stride) {
+    // in the order of the sorted list, by cell and insertion index: the sums then do
+    // not depend on the slots, which differ with the last rebuild and the tuning
+    for (int64_t q = gidx(); q < np; q += stride) {
+        const int64_t i = D.b.list[q];
         const double m = D.pt.rho[i] * sphere_volume(D.pt.d[i]);
         acc[8] += m * D.pt.u[i];
         acc[9] += m * D.pt.u[cap + i];
