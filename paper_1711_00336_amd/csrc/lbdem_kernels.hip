@@ -129,12 +129,13 @@ __device__ __forceinline__ int stencil_coord(int b, int o, int n, int per)
     return i < 0 ? 0 : (i >= n ? n - 1 : i);
 }
 
-// distinct wrapped coordinates c-r..c+r on one axis (walled: in range only)
+// distinct wrapped coordinates c-r..c+r on one axis, in this order also where
+// they are all cells of it, as the gather tiles take them (walled: in range only)
 __device__ __forceinline__ int axis_range(int c, int r, int n, int per, int *out, int cap)
 {
     int m = 0;
     if (per) {
-        if (2 * r + 1 >= n) {
+        if (2 * r + 1 > n) {
             for (int i = 0; i < n && m < cap; ++i) out[m++] = i;
         } else {
             for (int o = -r; o <= r; ++o) out[m++] = wrap1(c + o, n);
