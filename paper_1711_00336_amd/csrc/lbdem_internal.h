@@ -205,9 +205,9 @@ template <typename R>
 void launch_dem_substep_fused(const Desc &D, const Cells<R> &C, int k, int sub, hipStream_t s);
 void launch_reorder(const Desc &D, hipStream_t s);    // slots into list order if due
 bool dem_sorts_lengths(const Desc &D);
-// rebuild the Verlet lists if requested; judge: flag those that overflow (not where
+// rebuild the Verlet lists if requested; flag: mark those that overflow in Desc::flags (not where
 // only their lengths are wanted, before a step's own build)
-template <typename R> void launch_nlist(const Desc &D, hipStream_t s, bool judge = true);
+template <typename R> void launch_nlist(const Desc &D, hipStream_t s, bool flag = true);
 template <typename R>
 void launch_integrate(const Desc &D, const Cells<R> &C, int last_substep, int step_end, hipStream_t s);
 void launch_bin_count(const Desc &D, hipStream_t s);

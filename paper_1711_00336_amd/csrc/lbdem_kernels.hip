@@ -1562,10 +1562,10 @@ __device__ __forceinline__ void load_sphere(const DemRec<R> *pk, int64_t i, doub
 }
 
 // the list of slot i, by one wavefront; lds: 2 kListLds ints of its own. Neighbours
-// beyond the capacity raise FLAG_NLIST if `judge`.
+// beyond the capacity raise FLAG_NLIST if `flag`.
 template <typename R>
 __device__ __forceinline__ void build_list(const Desc &D, const DemRec<R> *pk, int64_t i, int lane, int *lds,
-                                           bool judge)
+                                           bool flag)
 {
     const Parts &P = D.pt;
     int *sid = lds, *ssl = lds + kListLds;
@@ -1638,7 +1638,7 @@ __device__ __forceinline__ void build_list(const Desc &D, const DemRec<R> *pk, i
         }
     }
     if (m > P.nbr) {
-        if (judge && lane == 0) atomicOr(D.flags, FLAG_NLIST);
+        if (flag && lane == 0) atomicOr(D.flags, FLAG_NLIST);
         m = P.nbr;
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -1671,7 +1671,7 @@ __device__ __forceinline__ void build_list(const Desc &D, const DemRec<R> *pk, i
     }
 }
 
-template <typename R> __global__ __launch_bounds__(kBlock) void k_nlist(Desc D, bool judge)
+template <typename R> __global__ __launch_bounds__(kBlock) void k_nlist(Desc D, bool flag)
 {
     __shared__ int lds[kBlock / 64][2 * kListLds];
     const Parts &P = D.pt;
@@ -1681,7 +1681,7 @@ template <typename R> __global__ __launch_bounds__(kBlock) void k_nlist(Desc D, 
     const int64_t per = (P.np + gridDim.x - 1) / gridDim.x, b0 = xcd_remap(blockIdx.x, gridDim.x) * per;
     const int64_t b1 = b0 + per < P.np ? b0 + per : P.np;
     for (int64_t i = b0 + wv; i < b1; i += kBlock / 64)
-        build_list<R>(D, (const DemRec<R> *)P.pk, i, lane, lds[wv], judge);
+        build_list<R>(D, (const DemRec<R> *)P.pk, i, lane, lds[wv], flag);
 }
 
 // what the last substep of a subcycle does besides integrating
@@ -3053,7 +3053,7 @@ void launch_reorder(const Desc &D, hipStream_t s)
     hipLaunchKernelGGL(k_reorder, dim3(nblocks(D.pt.np)), dim3(kBlock), 0, s, D);
     hipLaunchKernelGGL(k_reorder_back, dim3(nblocks(D.pt.np, kBlock)), dim3(kBlock), 0, s, D);
 }
-template <typename R> void launch_nlist(const Desc &D, hipStream_t s, bool judge)
+template <typename R> void launch_nlist(const Desc &D, hipStream_t s, bool flag)
 {
     if (D.pt.np <= 0) return;
     // few workgroups, as most launches find nothing to do (one wavefront per
@@ -3062,7 +3062,7 @@ template <typename R> void launch_nlist(const Desc &D, hipStream_t s, bool judge
     // one another per wavefront, the lists of 13.8 k spheres due every third
     // subcycle made it 0.99 ms long, not 0.77
     const int64_t nb = (D.pt.np + kBlock / 64 - 1) / (kBlock / 64);
-    hipLaunchKernelGGL(k_nlist<R>, dim3((unsigned)(nb < 2048 ? nb : 2048)), dim3(kBlock), 0, s, D, judge);
+    hipLaunchKernelGGL(k_nlist<R>, dim3((unsigned)(nb < 2048 ? nb : 2048)), dim3(kBlock), 0, s, D, flag);
 }
 template <typename R> void launch_integrate(const Desc &D, const Cells<R> &C, int last, int step_end, hipStream_t s)
 {

@@ -66,7 +66,7 @@ def _cluster_and_rest(d):
 
 @pytest.mark.parametrize("n_dem", [1, 3])
 def test_crowded_spheres_may_be_added_first(L, n_dem):
-    """Adding particles judges no list: lists that would overflow with the
+    """Adding particles flags no list: lists that would overflow with the
     first addition, and not with the second, are built by the first step."""
     from tests.parity_util import compare_states
     from oracle import oracle as O
